@@ -18,8 +18,23 @@ constexpr int TM = 32;            // mid-level tile side of the fused kernels
 constexpr int TT = 8;             // tiny tile side of the fused kernels (one point per thread and phase)
 constexpr int STRIP_BLOCK_W = 216; // columns of a streaming block (4 strips of 54)
 constexpr int GRID_THREADS = 256; // threads of the grid-wide kernels
-constexpr int ZEBRA_QUAD_LPW = 4; // lines per wave of the zebra line kernel on its largest levels
+constexpr int ZREG_N = 63;        // zebra line kernel: shortest line of the registers mapping
+// points per lane of that mapping, from the longest line of a launch
+inline int zebra_points(int n) { return n <= 255 ? 4 : n <= 511 ? 8 : 16; }
+// most lanes per line (log2) along direction dir (0 x, 1 y)
+__host__ __device__ inline int zebra_lg_most(int dir, bool quad) { return dir == 1 && quad ? 5 : 6; }
 constexpr int HIST_CAP = 8192;    // relres history entries kept per instance
+
+// place of point q in a table of n + 1 entries for that mapping: in order on shorter lines; from
+// ZTAB_LANES_N points (16 per lane) blocks of 1024 points hold, one vector of vn (16 bytes) after
+// the other, the vectors of the block's 64 lanes
+constexpr int ZTAB_LANES_N = 1023;
+inline int ztab_index(int n, int vn, int q)
+{
+    if (n < ZTAB_LANES_N) return q;
+    const int k = q & 15;
+    return (q & ~1023) + (k / vn * 64 + ((q >> 4) & 63)) * vn + k % vn;
+}
 
 // one level of one instance; arrays are row-major with leading dimension ld.
 // A holds the current estimate between calls, B is the second sweep buffer,
@@ -48,6 +63,8 @@ struct InstDev {
     const float* chol32;
     const double* zt64[MAXL];  // zebra line-solve tables of level d: reciprocal pivots, multipliers (x-lines), then (y-lines), n each
     const float* zt32[MAXL];
+    const double* zl64[MAXL];  // the same as ztab_index orders them, n + 1 entries each (levels with lines of >= ZREG_N points)
+    const float* zl32[MAXL];
     int32_t lds_off[MAXL]; // persistent kernel: element offset of level d's three (n+2)^2 arrays
     int32_t ops_beg[MAXL + 1]; // persistent kernel op list of a call with counter k = 1..MAXL+1
     int32_t ops_len[MAXL + 1];
@@ -205,7 +222,8 @@ enum GridKernel : int32_t {
     GK_GRAD = 20,      // -lam^T dS u / h^2 for theta and eps
     GK_ZERO_SELF = 22, // unfused: A[d] = 0 on the launch's own level
     GK_POSTPRE = 23,   // fused junction of sibling calls: post (nu2 = src) of the first + pre (nu) of the second
-    GK_ZEBRA = 24,     // zebra line relaxation in place on buffer src, lines of colour dst, direction nu (0 x, 1 y)
+    GK_ZEBRA = 24,     // zebra line relaxation in place on buffer src, lines of colour dst, direction nu (0 x, 1 y); zg and
+                       // flags: zebra_args
     GK_PCG_TRUE = 25,  // instances with check set: r = F - S u (FP64, replaces the recurrence residual), ||r||^2
 };
 

@@ -36,13 +36,13 @@ namespace kc {
 // ---------------------------------------------------------------------------
 // precision traits
 // ---------------------------------------------------------------------------
-template <typename T> struct P;
-template <> struct P<double> {
+template <typename T> struct Prec;
+template <> struct Prec<double> {
     static __device__ const double* s(const InstDev& I, int d) { return I.s64[d]; }
     static __device__ double w(const InstDev& I, int d) { return I.w64[d]; }
     static __device__ const double* chol(const InstDev& I) { return I.chol64; }
 };
-template <> struct P<float> {
+template <> struct Prec<float> {
     static __device__ const float* s(const InstDev& I, int d) { return I.s32[d]; }
     static __device__ float w(const InstDev& I, int d) { return I.w32[d]; }
     static __device__ const float* chol(const InstDev& I) { return I.chol32; }
@@ -182,6 +182,21 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
+// DPP lane moves (a VALU operand modifier, no LDS round trip); lanes whose source
+// lies outside the row or wave read 0.  A double moves as its two 32-bit halves.
+template <int CTRL> __device__ __forceinline__ float dpp(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL> __device__ __forceinline__ double dpp(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+constexpr int DPP_WAVE_SHR1 = 0x138;   // wave_shr:1 -> value of lane - 1 (0 in lane 0)
+constexpr int DPP_WAVE_SHL1 = 0x130;   // wave_shl:1 -> value of lane + 1 (0 in lane 63)
 struct Tile {
     int inst, blk, nblk, x0, y0;
 };
@@ -447,8 +462,8 @@ __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
     const int n = Lv.n;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     Sten<T> s;
-    s.load(P<T>::s(I, d));
-    const T w = P<T>::w(I, d);
+    s.load(Prec<T>::s(I, d));
+    const T w = Prec<T>::w(I, d);
     const T fs = (T)Lv.fscale;
     const T* F = (const T*)Lv.F;
     Acc2 nrm;
@@ -599,7 +614,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_semi(StageArgs a)
         return;
     }
     Sten<T> s;
-    s.load(P<T>::s(I, d));
+    s.load(Prec<T>::s(I, d));
     const T fs = (T)Lv.fscale;
     for (int k = ty; k < TY; k += GRID_THREADS / 64) {
         const int j = y0 + k;
@@ -660,22 +675,17 @@ __global__ void __launch_bounds__(GRID_THREADS) k_semi(StageArgs a)
 //   r; or the line's own y values and u) is issued before the chunk's stores,
 //   the neighbouring lines' values at q - 1, q, q + 1 slide through
 //   registers, and the chunk's d_q are formed before the recurrence.
-// * waves (levels at or above the threshold): two lines per wave (lanes 0-31
-//   and 32-63), eight per workgroup.  Lane l holds point q0 + (l mod 32) of a
-//   chunk of 32 points of its line: the lanes form the chunk's d_q (and load
-//   r) in parallel and put them in the wave's LDS slots; lanes 0 and 32 alone
-//   run the two recurrences over the chunk (unrolled, one LDS read per step,
-//   so the vector ALU issues only the recurrences' own operations, each
-//   advancing both lines, and the LDS returns 2 x 16 bytes per step), write
-//   the results back to LDS, and each lane stores its own point; the next
-//   chunk's loads are issued before the recurrences, so they are in flight
-//   while they run.  A level's n / 2 lines give n / 4 waves, against n / 128
-//   for the lane mapping, which is what large levels need to keep memory busy.  The backward pass
-//   reads each point's y back in the lane that wrote it.
+// * registers (levels at or above the threshold): zebra_regs below.
 // ---------------------------------------------------------------------------
 template <typename T> struct ZT;
-template <> struct ZT<double> { static __device__ const double* t(const InstDev& I, int d) { return I.zt64[d]; } };
-template <> struct ZT<float> { static __device__ const float* t(const InstDev& I, int d) { return I.zt32[d]; } };
+template <> struct ZT<double> {
+    static __device__ const double* t(const InstDev& I, int d) { return I.zt64[d]; }
+    static __device__ const double* lanes(const InstDev& I, int d) { return I.zl64[d]; }
+};
+template <> struct ZT<float> {
+    static __device__ const float* t(const InstDev& I, int d) { return I.zt32[d]; }
+    static __device__ const float* lanes(const InstDev& I, int d) { return I.zl32[d]; }
+};
 
 // per-line constants of one launch (direction DIR: 0 x-lines, 1 y-lines)
 template <typename T, int DIR>
@@ -757,207 +767,332 @@ __device__ __forceinline__ void zebra_lanes(const ZLine<T, DIR>& z)
     }
 }
 
-// the loads of one lane for a forward chunk: point q = q0 + lane (clamped
-// addresses).  The values are masked where the point or a neighbour is absent
-// only when d_q is formed, so that prefetched loads are not waited for early.
-template <typename T>
-struct ZFwd {
-    T m0, m1, m2, p0, p1, p2, f, r;
-    bool km0, km1, km2, kp0, kp1, kp2;   // which neighbour values are present
-    template <int DIR>
-    __device__ __forceinline__ void load(const ZLine<T, DIR>& z, int q)
+// the registers mapping.  A line of n points takes LN = min((n + 1) / P, 64) lanes of a wave, which
+// hold P consecutive points each in registers; lines of n + 1 > 64 P points go through chunks.  The
+// y-lines of levels from zebra_quad_n points (default 8191) take 32 lanes, so that a workgroup's eight
+// lines read 128-byte segments of a row: a colour takes 615 us instead of 760 at 8191^2 and 2.97 ms
+// instead of 3.95 at 16383^2, but 164 instead of 153 us at 4095^2 and 67 instead of 53 at 2047^2,
+// where the longer chain of the fewer waves costs more.
+//
+// What bounds a line is its chain of dependent operations (a fused multiply-add and a product
+// per point forward, a fused multiply-add backward).  Memory and LDS instructions between the
+// steps of a chain cost more than the steps do (about 15 cycles per LDS access against 11 for
+// the two operations), so here none are: every operand of a step is in the lane that takes it,
+// and the running value goes from one lane's points to the next lane's by one DPP move.  All
+// lanes run the chain over their own points in every round with whatever their west (backward:
+// east) neighbour holds; lane 0 of a line starts from the right value, so after round s lanes
+// 0 .. s hold the right results, unchanged by later rounds, and after LN rounds all do.
+//
+// A round costs about 50 cycles besides its points, the work before and after the chain is
+// proportional to P: P = 4 on levels of up to 255 points per line, 8 at 511, 16 above.
+// x-lines: with P = 16 and whole waves the rows are read in the order of memory and handed to
+// their lanes through LDS; shorter lines are read by their lanes directly.  y-lines: a thread
+// forms the right-hand sides of P rows of one line, neighbouring threads taking neighbouring
+// lines of the workgroup, and hands them over through LDS.  y of a chunk that is not the last
+// waits in the line's own array, where each thread reads back the points it wrote.  n + 1 is a
+// power of two, so only the last lane of a line holds a point past its end (q = n): it enters
+// with u = 0 and y = 0, which leaves every other value exactly as the elimination defines it.
+template <int P> __device__ __forceinline__ int zstage(int seg) { return seg * (P + 1) + (seg >> 6) * 16; }
+
+template <typename T, int DIR, int P>
+struct ZRegs {
+    gp<T> V;
+    gp<const T> F, rpv, mul;     // rpv, mul: the level's tables in lane order (ztab_index)
+    int n, nl, ldv, ldf;         // points per line, lines of the level
+    int line0;                   // first line of the workgroup; its slot s is line line0 + 2 s
+    int lgln;                    // log2 lanes per line
+    T fs, lo, cm0, cm1, cm2, cp0, cp1, cp2;
+    T* st;                       // LDS stage
+
+    __device__ __forceinline__ int lane() const { return threadIdx.x & 63; }
+    __device__ __forceinline__ int place() const { return threadIdx.x & ((1 << lgln) - 1); }   // the lane's place in its line
+    __device__ __forceinline__ int line() const { return line0 + 2 * (int)(threadIdx.x >> lgln); }
+    __device__ __forceinline__ int q0(int ch) const { return ((ch << lgln) + place()) * P; }   // its first point
+    __device__ __forceinline__ bool staged_x() const { return P == 16 && lgln == 6; }
+    // y-lines, order of memory: this thread takes P rows from q of line L, for the lane at `seg`
+    __device__ __forceinline__ void at_y(int ch, int& seg, int& L, int& q) const
     {
-        const int qc = min(q, z.n - 1), qm = max(qc - 1, 0), qp = min(q + 1, z.n - 1);
-        m0 = z.V[z.vi(z.Lm, qm)];
-        m1 = z.V[z.vi(z.Lm, qc)];
-        m2 = z.V[z.vi(z.Lm, qp)];
-        p0 = z.V[z.vi(z.Lp, qm)];
-        p1 = z.V[z.vi(z.Lp, qc)];
-        p2 = z.V[z.vi(z.Lp, qp)];
-        f = z.F[z.fi(qc)];
-        r = z.rpv[qc];
-        km0 = z.hm && q >= 1;
-        km1 = z.hm;
-        km2 = z.hm && q + 1 < z.n;
-        kp0 = z.hp && q >= 1;
-        kp1 = z.hp;
-        kp2 = z.hp && q + 1 < z.n;
+        const int lgs = 8 - lgln, slot = threadIdx.x & ((1 << lgs) - 1), run = threadIdx.x >> lgs;
+        seg = (slot << lgln) + run;
+        L = line0 + 2 * slot;
+        q = ((ch << lgln) + run) * P;
     }
-    template <int DIR>
-    __device__ __forceinline__ T dq(const ZLine<T, DIR>& z) const
+    // x-lines, order of memory: the stage place of this lane's point 64 i + lane of the wave's 1024
+    __device__ __forceinline__ T* stage_x(int i) const
     {
-        T acc = T(0);
-        acc = fmadd(z.cm0, (km0 ? m0 : T(0)), acc);
-        acc = fmadd(z.cm1, (km1 ? m1 : T(0)), acc);
-        acc = fmadd(z.cm2, (km2 ? m2 : T(0)), acc);
-        acc = fmadd(z.cp0, (kp0 ? p0 : T(0)), acc);
-        acc = fmadd(z.cp1, (kp1 ? p1 : T(0)), acc);
-        acc = fmadd(z.cp2, (kp2 ? p2 : T(0)), acc);
-        return z.fs * f - acc;
+        return st + zstage<P>((threadIdx.x & ~63u) + (lane() >> 4)) + (lane() & 15) + i * 4 * (P + 1);
+    }
+    __device__ __forceinline__ void put(const T (&x)[P], int seg) const
+    {
+        T* const s = st + zstage<P>(seg);
+#pragma unroll
+        for (int k = 0; k < P; ++k) s[k] = x[k];
+    }
+    __device__ __forceinline__ void get(T (&x)[P], int seg) const
+    {
+        const T* const s = st + zstage<P>(seg);
+#pragma unroll
+        for (int k = 0; k < P; ++k) x[k] = s[k];
+    }
+    // this lane's entries of a table
+    __device__ __forceinline__ void table(gp<const T> t, int ch, T (&x)[P]) const
+    {
+        constexpr int VN = 16 / sizeof(T);
+        typedef T vec __attribute__((ext_vector_type(VN)));
+        const bool lanes = n >= ZTAB_LANES_N;   // blocks of 64 lanes' 16 points, vector by vector
+        const int gl = (ch << lgln) + place();
+        const gp<const vec> v = (gp<const vec>)t + (lanes ? (gl >> 6) * (64 * 16 / VN) + (gl & 63) : gl * (P / VN));
+        const int st = lanes ? 64 : 1;
+#pragma unroll
+        for (int k = 0; k < P / VN; ++k) {
+            const vec e = v[k * st];
+#pragma unroll
+            for (int j = 0; j < VN; ++j) x[VN * k + j] = e[j];
+        }
+    }
+    // the three products of each of P points with one neighbouring line's values w (q - 1 .. q + P)
+    static __device__ __forceinline__ void products(T c0, T c1, T c2, const T (&w)[P + 2], T (&acc)[P])
+    {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            acc[k] = fmadd(c0, w[k], acc[k]);
+            acc[k] = fmadd(c1, w[k + 1], acc[k]);
+            acc[k] = fmadd(c2, w[k + 2], acc[k]);
+        }
+    }
+    // zeros before the line's first point, from its end on, and for an absent line
+    static __device__ __forceinline__ void mask(T (&w)[P + 2], bool first, bool last, bool have)
+    {
+        if (first) w[0] = T(0);
+        if (last) w[P] = w[P + 1] = T(0);
+        if (!have) {
+#pragma unroll
+            for (int k = 0; k < P + 2; ++k) w[k] = T(0);
+        }
+    }
+    // points q - 1 .. q + P of a row, stride st between points, addresses clamped to the line
+    static __device__ __forceinline__ void window(gp<const T> p, ptrdiff_t st, bool first, bool last, T (&w)[P + 2])
+    {
+        w[0] = p[first ? 0 : -st];
+#pragma unroll
+        for (int k = 0; k < P - 1; ++k) w[k + 1] = p[k * st];
+        w[P] = p[(last ? P - 2 : P - 1) * st];
+        w[P + 1] = p[(last ? P - 2 : P) * st];
+    }
+    // right-hand sides d of this lane's points of a chunk
+    __device__ __forceinline__ void rhs(int ch, T (&d)[P]) const
+    {
+        T acc[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) acc[k] = T(0);
+        int seg, L, q;
+        if constexpr (DIR == 0) {
+            L = line();
+            q = q0(ch);
+        } else {
+            at_y(ch, seg, L, q);
+        }
+        const bool hm = L > 0, hp = L + 1 < nl, first = q == 0, last = q + P > n;
+        const int Lc = min(L, nl - 1), Lm = max(Lc - 1, 0), Lp = min(Lc + 1, nl - 1);
+        if (DIR == 0 && staged_x()) {
+            if constexpr (P == 16) {
+                const int qb = ch * 1024 + lane(), qe = min(qb + 15 * 64, n - 1);
+                const gp<const T> pm = V + (size_t)Lm * ldv, pp = V + (size_t)Lp * ldv, pf = F + (size_t)Lc * ldf;
+                T m[P], p[P], f[P];
+#pragma unroll
+                for (int i = 0; i < P; ++i) m[i] = pm[i < P - 1 ? qb + i * 64 : qe];
+#pragma unroll
+                for (int i = 0; i < P; ++i) p[i] = pp[i < P - 1 ? qb + i * 64 : qe];
+#pragma unroll
+                for (int i = 0; i < P; ++i) f[i] = pf[i < P - 1 ? qb + i * 64 : qe];
+                // the points beside the wave's 1024, for its first and last lanes
+                const int qs = lane() == 0 ? max(ch * 1024 - 1, 0) : min(ch * 1024 + 1024, n - 1);
+                const T me = pm[qs], pe = pp[qs];
+                const int sg = threadIdx.x;
+                auto hand = [&](const T (&v)[P]) {
+#pragma unroll
+                    for (int i = 0; i < P; ++i) *stage_x(i) = v[i];
+                    wave_sync();
+                };
+                auto side = [&](const T (&v)[P], T edge, bool have, T c0, T c1, T c2) {
+                    T w[P + 2];
+                    hand(v);
+                    const T* const s = st + zstage<P>(sg);
+#pragma unroll
+                    for (int k = 0; k < P; ++k) w[k + 1] = s[k];
+                    const T west = st[lane() == 0 ? 0 : zstage<P>(sg - 1) + P - 1], east = st[lane() == 63 ? 0 : zstage<P>(sg + 1)];
+                    wave_sync();
+                    w[0] = lane() == 0 ? edge : west;
+                    w[P + 1] = lane() == 63 ? edge : east;
+                    mask(w, first, last, have);
+                    products(c0, c1, c2, w, acc);
+                };
+                side(m, me, hm, cm0, cm1, cm2);
+                side(p, pe, hp, cp0, cp1, cp2);
+                hand(f);
+                get(d, sg);
+                wave_sync();
+            }
+        } else {
+            const ptrdiff_t sv = DIR == 0 ? 1 : ldv, sf = DIR == 0 ? 1 : ldf;
+            const gp<const T> base = V + (DIR == 0 ? (size_t)q : (size_t)q * ldv);
+            T m[P + 2], p[P + 2];
+            window(base + (DIR == 0 ? (size_t)Lm * ldv : (size_t)Lm), sv, first, last, m);
+            window(base + (DIR == 0 ? (size_t)Lp * ldv : (size_t)Lp), sv, first, last, p);
+            const gp<const T> pf = F + (DIR == 0 ? (size_t)Lc * ldf + q : (size_t)q * ldf + Lc);
+#pragma unroll
+            for (int k = 0; k < P; ++k) d[k] = pf[(k == P - 1 && last ? P - 2 : k) * sf];
+            mask(m, first, last, hm);
+            mask(p, first, last, hp);
+            products(cm0, cm1, cm2, m, acc);
+            products(cp0, cp1, cp2, p, acc);
+        }
+#pragma unroll
+        for (int k = 0; k < P; ++k) d[k] = fs * d[k] - acc[k];
+        if constexpr (DIR == 1) {
+            put(d, seg);
+            __syncthreads();
+            get(d, threadIdx.x);
+            __syncthreads();
+        }
+    }
+    // y of an earlier chunk, as store() left it in the line (whole waves: LN = 64)
+    __device__ __forceinline__ void reload(int ch, T (&y)[P]) const
+    {
+        if constexpr (DIR == 0) {
+            const gp<const T> p = V + (size_t)min(line(), nl - 1) * ldv;
+            if (staged_x()) {
+                if constexpr (P == 16) {
+                    T v[P];
+#pragma unroll
+                    for (int i = 0; i < P; ++i) v[i] = p[ch * 1024 + i * 64 + lane()];
+#pragma unroll
+                    for (int i = 0; i < P; ++i) *stage_x(i) = v[i];
+                    wave_sync();
+                    get(y, threadIdx.x);
+                    wave_sync();
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < P; ++k) y[k] = p[q0(ch) + k];
+            }
+        } else {
+            int seg, L, q;
+            at_y(ch, seg, L, q);
+            const gp<const T> p = V + (size_t)q * ldv + min(L, nl - 1);
+#pragma unroll
+            for (int k = 0; k < P; ++k) y[k] = p[(size_t)k * ldv];
+            put(y, seg);
+            __syncthreads();
+            get(y, threadIdx.x);
+            __syncthreads();
+        }
+    }
+    // the lanes' values of a chunk back to the line
+    __device__ __forceinline__ void store(int ch, const T (&x)[P]) const
+    {
+        if constexpr (DIR == 0) {
+            const int L = line();
+            const gp<T> p = V + (size_t)L * ldv;
+            if (staged_x()) {
+                if constexpr (P == 16) {
+                    put(x, threadIdx.x);
+                    wave_sync();
+                    T v[P];
+#pragma unroll
+                    for (int i = 0; i < P; ++i) v[i] = *stage_x(i);
+                    wave_sync();
+                    const int qb = ch * 1024 + lane();
+                    if (L < nl) {
+#pragma unroll
+                        for (int i = 0; i < P - 1; ++i) p[qb + i * 64] = v[i];
+                        if (qb + 15 * 64 < n) p[qb + 15 * 64] = v[P - 1];
+                    }
+                }
+            } else if (L < nl) {
+                const int q = q0(ch);
+#pragma unroll
+                for (int k = 0; k < P - 1; ++k) p[q + k] = x[k];
+                if (q + P <= n) p[q + P - 1] = x[P - 1];
+            }
+        } else {
+            put(x, threadIdx.x);
+            __syncthreads();
+            int seg, L, q;
+            at_y(ch, seg, L, q);
+            T v[P];
+            get(v, seg);
+            __syncthreads();
+            const gp<T> p = V + (size_t)q * ldv + L;
+            if (L < nl) {
+#pragma unroll
+                for (int k = 0; k < P - 1; ++k) p[(size_t)k * ldv] = v[k];
+                if (q + P <= n) p[(size_t)(P - 1) * ldv] = v[P - 1];
+            }
+        }
     }
 };
 
-// a wave's LDS slots for one chunk of each of its 64 / ZC lines: the lanes' (d_q, r_q)
-// or (y_q, u_q) pairs, read back one per step by the lane running that line's
-// recurrence, and the chunk's results, written by that lane and read by every
-// lane of the line.  ZC (points per chunk and line) is 32 (two lines per wave) or
-// 16 (four lines per wave); the slots of a wave take the same bytes either way
-template <typename T, int ZC>
-struct ZSlots {
-    T pair[64 / ZC][ZC][2];
-    T res[64 / ZC][ZC];
-};
-
-template <typename T, int DIR, int ZC>
-__device__ __forceinline__ void zebra_wave(const ZLine<T, DIR>& z, ZSlots<T, ZC>& sl)
+template <typename T, int DIR, int P>
+__device__ __forceinline__ void zebra_regs(const ZRegs<T, DIR, P>& z)
 {
-    static_assert(ZC == 32 || ZC == 16, "a line takes half or a quarter of a wave");
-    constexpr int SB = 8;   // steps per block: the block's pairs are read one block ahead
-    const int n = z.n, lane = threadIdx.x & 63, h = lane / ZC, p = lane & (ZC - 1);
-    const bool runner = p == 0;   // the first lane of each line's group runs its recurrence
-    ZFwd<T> cur;
-    cur.load(z, p);
-    T prev = T(0);
-    // one chunk of the forward pass.  Every chunk issues the same memory operations (the next
-    // chunk's loads, clamped past the line's end, then one store), and the first chunk runs
-    // before the loop: the loop is then entered, like its back edge, with one store behind
-    // the loads, so the wait for them need not cover that store
-    auto fwd = [&](int q0) {
-        sl.pair[h][p][0] = cur.dq(z);
-        sl.pair[h][p][1] = cur.r;
-        wave_sync();
-        cur.load(z, q0 + ZC + p);   // in flight during the recurrence
-        const int cnt = min(ZC, n - q0);
-        const bool first = q0 == 0;
-        // a full chunk keeps every step; in the last one, steps past the line's end
-        // (k >= cnt) compute values that are neither kept nor stored
-        auto steps = [&](auto partial) {
-            T dk[SB], rk[SB];   // the block's pairs, read one block ahead of the recurrence
+    const int LN = 1 << z.lgln, lane = z.lane(), nch = (z.n + 1) >> (z.lgln + (P == 16 ? 4 : P == 8 ? 3 : 2));
+    const bool west = z.place() == 0, east = z.place() == LN - 1;   // the line's ends
+    T y[P], t[P];
+    // y_0 = d_0 r_0: with prev = +-0 of lo's sign the first step's product is -0, which changes no d_0
+    T start = __builtin_signbit(z.lo) ? -T(0) : T(0);
+    for (int ch = 0; ch < nch; ++ch) {
+        z.table(z.rpv, ch, t);
+        z.rhs(ch, y);
+        T prev = T(0);
+        for (int s = 1; s < LN; ++s) {
+            T v = dpp<DPP_WAVE_SHR1>(prev);
+            v = west ? start : v;
 #pragma unroll
-            for (int j = 0; j < SB; ++j) {
-                dk[j] = sl.pair[h][j][0];
-                rk[j] = sl.pair[h][j][1];
-            }
-#pragma unroll
-            for (int kb = 0; kb < ZC; kb += SB) {
-                T dn[SB], rn[SB];
-                if (kb + SB < ZC) {
-#pragma unroll
-                    for (int j = 0; j < SB; ++j) {
-                        dn[j] = sl.pair[h][kb + SB + j][0];
-                        rn[j] = sl.pair[h][kb + SB + j][1];
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < SB; ++j) {
-                    const int k = kb + j;
-                    const T t = (k == 0 && first) ? dk[j] : fmadd(-z.lo, prev, dk[j]);   // y_0 = d_0 r_0
-                    const T y = t * rk[j];
-                    sl.res[h][k] = y;
-                    if constexpr (decltype(partial)::value) prev = (k < cnt) ? y : prev;
-                    else prev = y;
-                }
-                if (kb + SB < ZC) {
-#pragma unroll
-                    for (int j = 0; j < SB; ++j) {
-                        dk[j] = dn[j];
-                        rk[j] = rn[j];
-                    }
-                }
-            }
-        };
-        // the runner lanes run the recurrences: each instruction advances every line of the
-        // wave, and the LDS returns 16 bytes per line and step
-        if (runner) {
-            if (cnt == ZC) steps(std::false_type{});
-            else steps(std::true_type{});
+            for (int k = 0; k < P; ++k) v = fmadd(-z.lo, v, y[k]) * t[k];
+            prev = v;
         }
-        wave_sync();
-        {   // lanes past the line's end store the last point's value again (same value, same address)
-            const int k = min(p, cnt - 1);
-            z.V[z.vi(z.line, q0 + k)] = sl.res[h][k];
+        T v = dpp<DPP_WAVE_SHR1>(prev);
+        v = west ? start : v;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            v = fmadd(-z.lo, v, y[k]) * t[k];
+            y[k] = v;
         }
-        wave_sync();   // the slots are rewritten by the next chunk
-    };
-    fwd(0);
-    for (int q0 = ZC; q0 < n; q0 += ZC) fwd(q0);
-
-    // backward, chunks from the last one down; a lane owns the points it wrote above
-    const int c_last = (n - 1) / ZC;
-    const T ylast = __shfl(prev, lane & (64 - ZC), 64);   // y_{n-1}, kept by the line's runner lane
-    T next = prev;   // x_{n-1} = y_{n-1} (runner lanes)
-    T yv, uv;
-    {
-        const int q = min(c_last * ZC + p, n - 1);
-        yv = z.V[z.vi(z.line, q)];
-        uv = z.mul[q];
+        if (ch + 1 < nch) {
+            start = __shfl(v, lane | (LN - 1), 64);
+            z.store(ch, y);
+        }
     }
-    auto bwd = [&](int c) {
-        const int q0 = c * ZC;
-        sl.pair[h][p][0] = yv;
-        sl.pair[h][p][1] = uv;
-        wave_sync();
-        {   // in flight during the recurrence (every chunk issues it; clamped before the line's start)
-            const int q = max(q0 - ZC + p, 0);
-            yv = z.V[z.vi(z.line, q)];
-            uv = z.mul[q];
+    if (east) y[P - 1] = T(0);   // the point past the line's end
+    start = T(0);
+    for (int ch = nch - 1; ch >= 0; --ch) {
+        z.table(z.mul, ch, t);
+        if (ch + 1 < nch) z.reload(ch, y);
+        T next = T(0);
+        for (int s = 1; s < LN; ++s) {
+            T v = dpp<DPP_WAVE_SHL1>(next);
+            v = east ? start : v;
+#pragma unroll
+            for (int k = P - 1; k >= 0; --k) v = fmadd(-t[k], v, y[k]);
+            next = v;
         }
-        const int top = min(ZC - 1, n - 2 - q0);   // x_{n-1} = y_{n-1} is already in place
-        auto steps = [&](auto partial) {
-            T yk[SB], uk[SB];   // the block's pairs, read one block ahead of the recurrence
+        T v = dpp<DPP_WAVE_SHL1>(next);
+        v = east ? start : v;
 #pragma unroll
-            for (int j = 0; j < SB; ++j) {
-                yk[j] = sl.pair[h][ZC - SB + j][0];
-                uk[j] = sl.pair[h][ZC - SB + j][1];
-            }
-#pragma unroll
-            for (int kb = ZC - SB; kb >= 0; kb -= SB) {
-                T yn[SB], un[SB];
-                if (kb > 0) {
-#pragma unroll
-                    for (int j = 0; j < SB; ++j) {
-                        yn[j] = sl.pair[h][kb - SB + j][0];
-                        un[j] = sl.pair[h][kb - SB + j][1];
-                    }
-                }
-#pragma unroll
-                for (int j = SB - 1; j >= 0; --j) {
-                    const int k = kb + j;
-                    const T x = fmadd(-uk[j], next, yk[j]);
-                    sl.res[h][k] = x;
-                    if constexpr (decltype(partial)::value) next = (k <= top) ? x : next;
-                    else next = x;
-                }
-                if (kb > 0) {
-#pragma unroll
-                    for (int j = 0; j < SB; ++j) {
-                        yk[j] = yn[j];
-                        uk[j] = un[j];
-                    }
-                }
-            }
-        };
-        if (runner) {
-            if (top == ZC - 1) steps(std::false_type{});
-            else steps(std::true_type{});
+        for (int k = P - 1; k >= 0; --k) {
+            v = fmadd(-t[k], v, y[k]);
+            y[k] = v;
         }
-        wave_sync();
-        {   // lanes past top store the value at top again; with top = -1 (a chunk holding only
-            // the line's last point) every lane stores y_{n-1} back in place
-            const int k = min(p, max(top, 0));
-            const T xv = top >= 0 ? sl.res[h][k] : ylast;
-            z.V[z.vi(z.line, q0 + k)] = xv;
-        }
-        wave_sync();
-    };
-    bwd(c_last);
-    for (int c = c_last - 1; c >= 0; --c) bwd(c);
+        if (ch > 0) start = __shfl(v, lane & ~(LN - 1), 64);
+        z.store(ch, y);
+    }
 }
 
-template <typename T, int DIR>
+// P: points per lane of the registers mapping; 0: no instance of the launch takes it
+template <typename T, int DIR, int P>
 __global__ void __launch_bounds__(GRID_THREADS) k_zebra(StageArgs a)
 {
-    __shared__ ZSlots<T, 32> slots[GRID_THREADS / 64];
     const int b = blockIdx.x;
     const int inst = find_inst(a.tile_off, a.count, b);
     if (a.st[inst].done) return;
@@ -965,42 +1100,62 @@ __global__ void __launch_bounds__(GRID_THREADS) k_zebra(StageArgs a)
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const int n = Lv.n, nx = Lv.nx;   // lines and points per line (equal except on semi-coarsened levels)
-    // the launch's thresholds (flags: bits 0-14 two lines per wave from this line length,
-    // bits 15-29 four lines per wave) pick the mapping for this instance from the line
-    // length; the block table was sized the same way
-    const int wave_n = a.flags & 0x7fff, quad_n = (a.flags >> 15) & 0x7fff;
-    const bool waves = wave_n > 0 && nx >= wave_n;
-    const bool quad = waves && quad_n > 0 && nx >= quad_n;
-    int blk = b - a.tile_off[inst];
-    int line;
-    if (waves) {
-        // consecutive line groups on one XCD (workgroups go round-robin over the
-        // eight XCDs), so y-lines sharing cache lines share an L2
-        const int nb = a.tile_off[inst + 1] - a.tile_off[inst];
-        if ((a.tile_off[inst] & 7) == 0 && (nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
-        // lpw lines per wave, 64 / lpw lanes each; a line past the level's last one repeats
-        // the wave's first (the same values go to the same addresses again)
-        const int lpw = quad ? ZEBRA_QUAD_LPW : 2;
-        const int first = 2 * (blk * (GRID_THREADS / 64) * lpw + lpw * (int)(threadIdx.x >> 6)) + a.dst;
-        if (first >= n) return;   // the whole wave
-        line = first + 2 * (int)((threadIdx.x & 63) / (64 / lpw));
-        if (line >= n) line = first;
-    } else {
-        if (threadIdx.x >= 64) return;
-        line = 2 * (blk * 64 + (int)threadIdx.x) + a.dst;
+    const int toff = a.tile_off[inst];
+    int blk = b - toff;
+    Sten<T> s;
+    s.load(Prec<T>::s(I, d));
+    const gp<T> V = glob<T>(buf<T>(Lv, a.src));
+    const gp<const T> F = glob<T>((const void*)Lv.F);
+    const int ldv = a.src ? Lv.ldb : Lv.lda;   // element offsets fit 32 bits (n <= 2^14)
+    if constexpr (P > 0) {
+        // flags: bits 0-14 the line length from which an instance takes the registers mapping (0 never),
+        // bits 15-29 that from which its y-lines take half as many lanes (0 never)
+        const int from = a.flags & 0x7fff, quad_n = (a.flags >> 15) & 0x7fff;
+        if (from > 0 && nx >= from) {
+            __shared__ T stage[GRID_THREADS * (P + 1) + 64];
+            ZRegs<T, DIR, P> z;
+            z.lgln = min(31 - __clz(nx + 1) - (P == 16 ? 4 : P == 8 ? 3 : 2), zebra_lg_most(DIR, quad_n > 0 && nx >= quad_n));
+            const int nb = ((n + 1) / 2 + (GRID_THREADS >> z.lgln) - 1) >> (8 - z.lgln);
+            if (blk >= nb) return;   // the table is sized for 64 lanes per line
+            // consecutive line groups on one XCD (workgroups go round-robin over the
+            // eight XCDs), so y-lines sharing cache lines share an L2
+            if ((toff & 7) == 0 && (nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
+            z.line0 = 2 * (blk << (8 - z.lgln)) + a.dst;
+            // a wave (x-lines; nothing of theirs is shared) or workgroup without a line
+            if (DIR == 0 ? z.line() >= n : z.line0 >= n) return;
+            z.V = V;
+            z.F = F;
+            z.rpv = glob<T>((const void*)(ZT<T>::lanes(I, d) + (size_t)DIR * 2 * (nx + 1)));
+            z.mul = z.rpv + nx + 1;
+            z.n = nx;
+            z.nl = n;
+            z.ldv = ldv;
+            z.ldf = Lv.ldf;
+            z.fs = (T)Lv.fscale;
+            z.lo = DIR == 0 ? s.c[3] : s.c[1];
+            z.cm0 = s.c[0];
+            z.cm1 = DIR == 0 ? s.c[1] : s.c[3];
+            z.cm2 = DIR == 0 ? s.c[2] : s.c[6];
+            z.cp0 = DIR == 0 ? s.c[6] : s.c[2];
+            z.cp1 = DIR == 0 ? s.c[7] : s.c[5];
+            z.cp2 = s.c[8];
+            z.st = stage;
+            zebra_regs<T, DIR, P>(z);
+            return;
+        }
     }
+    if (threadIdx.x >= 64) return;
+    const int line = 2 * (blk * 64 + (int)threadIdx.x) + a.dst;
     if (line >= n) return;
     ZLine<T, DIR> z;
-    z.V = glob<T>(buf<T>(Lv, a.src));
-    z.ldv = a.src ? Lv.ldb : Lv.lda;   // element offsets fit 32 bits (n <= 2^14)
+    z.V = V;
+    z.ldv = ldv;
     z.ldf = Lv.ldf;
-    z.F = glob<T>((const void*)Lv.F);
+    z.F = F;
     z.fs = (T)Lv.fscale;
     z.n = nx;
     z.nl = n;
     z.line = line;
-    Sten<T> s;
-    s.load(P<T>::s(I, d));
     z.rpv = glob<T>((const void*)(ZT<T>::t(I, d) + (size_t)DIR * 2 * nx));
     z.mul = z.rpv + nx;
     z.lo = DIR == 0 ? s.c[3] : s.c[1];
@@ -1015,15 +1170,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_zebra(StageArgs a)
     z.hp = line + 1 < n;   // n lines
     z.Lm = z.hm ? line - 1 : line;   // clamped; values masked when absent
     z.Lp = z.hp ? line + 1 : line;
-    if (quad) {
-        using QS = ZSlots<T, 64 / ZEBRA_QUAD_LPW>;
-        static_assert(sizeof(QS) == sizeof(ZSlots<T, 32>), "one slot array serves both mappings");
-        zebra_wave<T, DIR, 64 / ZEBRA_QUAD_LPW>(z, *reinterpret_cast<QS*>(&slots[threadIdx.x >> 6]));
-    } else if (waves) {
-        zebra_wave<T, DIR, 32>(z, slots[threadIdx.x >> 6]);
-    } else {
-        zebra_lanes<T, DIR>(z);
-    }
+    zebra_lanes<T, DIR>(z);
 }
 
 // ---------------------------------------------------------------------------
@@ -1128,8 +1275,8 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     const T fs = (T)Lv.fscale;
     const int rx0 = t.x0 - H, ry0 = t.y0 - H;
     Sten<T> s;
-    s.load(P<T>::s(I, d));
-    const T w = P<T>::w(I, d);
+    s.load(Prec<T>::s(I, d));
+    const T w = Prec<T>::w(I, d);
     const bool zg = a.zg != 0;
     // a zero guess reads no estimate: F, with its own leading dimension, is a valid stand-in address
     const gp<const T> Av = zg ? F : A;
@@ -1254,8 +1401,8 @@ __global__ void __launch_bounds__(GRID_THREADS) k_post(StageArgs a)
     const int rx0 = t.x0 - H, ry0 = t.y0 - H;
     const int cx0 = (rx0 - 1) >> 1, cy0 = (ry0 - 1) >> 1;
     Sten<T> s;
-    s.load(P<T>::s(I, d));
-    const T w = P<T>::w(I, d);
+    s.load(Prec<T>::s(I, d));
+    const T w = Prec<T>::w(I, d);
 
     {   // every load of the region in flight before the LDS stores
         constexpr int NR = RH * RW, NPT = (NR + GRID_THREADS - 1) / GRID_THREADS;
@@ -1363,8 +1510,8 @@ __global__ void __launch_bounds__(GRID_THREADS) k_postpre(StageArgs a)
     const int rx0 = t.x0 - H, ry0 = t.y0 - H;
     const int cx0 = (rx0 - 1) >> 1, cy0 = (ry0 - 1) >> 1;
     Sten<T> s;
-    s.load(P<T>::s(I, d));
-    const T w = P<T>::w(I, d);
+    s.load(Prec<T>::s(I, d));
+    const T w = Prec<T>::w(I, d);
 
     {   // every load of the region in flight before the LDS stores
         constexpr int NR = RH * RW, NPT = (NR + GRID_THREADS - 1) / GRID_THREADS;
@@ -1482,22 +1629,6 @@ __device__ inline void chol_solve_padded(int n, const T* Lc, const T* F, T* v, i
 // overlap.  Arithmetic per point is the tile kernels' (same expressions, same
 // order), so results are identical.
 // ---------------------------------------------------------------------------
-// DPP lane moves (a VALU operand modifier, no LDS round trip); lanes whose source
-// lies outside the row or wave read 0.  A double moves as its two 32-bit halves.
-template <int CTRL> __device__ __forceinline__ float dpp(float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL> __device__ __forceinline__ double dpp(double x)
-{
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-constexpr int DPP_WAVE_SHR1 = 0x138;   // wave_shr:1 -> value of lane - 1 (0 in lane 0)
-constexpr int DPP_WAVE_SHL1 = 0x130;   // wave_shl:1 -> value of lane + 1 (0 in lane 63)
-
 constexpr int SW = 54;        // output columns per wave (pre-smoothing with nu <= 3 fits 64 lanes)
 constexpr int SWAVES = 4;     // strips per block, side by side
 static_assert(SW * SWAVES == STRIP_BLOCK_W, "strip geometry");
@@ -1637,8 +1768,8 @@ __global__ void __launch_bounds__(256) k_pre_s(StageArgs a)
     const int lda = Lv.lda, ldf = Lv.ldf, ldb = Lv.ldb, ldc = Lc.ldf;
     const T fs = (T)Lv.fscale;
     Sten<T> s;
-    s.load(P<T>::s(I, d));
-    const T w = P<T>::w(I, d);
+    s.load(Prec<T>::s(I, d));
+    const T w = Prec<T>::w(I, d);
     const bool zg = a.zg != 0, stop = a.fin == FIN_STOP;
     const int lane = threadIdx.x & 63;
     const int x = t.x0 - H + lane;
@@ -1777,8 +1908,8 @@ __global__ void __launch_bounds__(256) k_post_s(StageArgs a)
     const int lda = Lv.lda, ldf = Lv.ldf, ldb = Lv.ldb, ldc = Lc.lda;
     const T fs = (T)Lv.fscale;
     Sten<T> s;
-    s.load(P<T>::s(I, d));
-    const T w = P<T>::w(I, d);
+    s.load(Prec<T>::s(I, d));
+    const T w = Prec<T>::w(I, d);
     const int lane = threadIdx.x & 63;
     const int x = t.x0 - H + lane;
     const bool col = t.live && (unsigned)x < (unsigned)n;
@@ -2580,7 +2711,7 @@ struct Sub {
     __device__ __forceinline__ void solve(int d, int lg, int off)
     {
         const int n = (1 << lg) - 1;
-        const T* Lc = (n * n * n * n <= SubParams<T>::CH) ? pp->chol : P<T>::chol(*I);
+        const T* Lc = (n * n * n * n <= SubParams<T>::CH) ? pp->chol : Prec<T>::chol(*I);
         if (threadIdx.x == 0) chol_solve_padded<T>(n, Lc, bufp(off, lg, 2), bufp(off, lg, (cur >> d) & 1), n + 2);
         sync_lg(lg);
     }
@@ -2699,7 +2830,7 @@ __global__ void __launch_bounds__(THREADS) k_subtree(SubArgs a)
     const gp<T> Ag = glob<T>(fast ? a.A0 : Lv.A);
     const int ldf = fast ? a.ldf0 : Lv.ldf, lda = fast ? a.lda0 : Lv.lda;
     const int sub_lds = fast ? a.sub_lds : I.sub_lds;
-    const T* const chol = fast ? (const T*)a.chol0 : P<T>::chol(I);
+    const T* const chol = fast ? (const T*)a.chol0 : Prec<T>::chol(I);
     const bool zero = a.pair || a.zg;
     const int k1 = min(a.kappa, MAXL + 1), k2 = min(max(a.kappa - 1, 1), MAXL + 1);
     // zebra calls use op lists without register calls
@@ -2717,11 +2848,11 @@ __global__ void __launch_bounds__(THREADS) k_subtree(SubArgs a)
         }
         for (int t = threadIdx.x; t < MAXL * 9; t += blockDim.x) {
             const int d = t / 9;
-            pp.s[d][t % 9] = (d < L) ? P<T>::s(I, d)[t % 9] : T(0);
+            pp.s[d][t % 9] = (d < L) ? Prec<T>::s(I, d)[t % 9] : T(0);
         }
         if (threadIdx.x < MAXL) {
             const int d = threadIdx.x;
-            pp.w[d] = (d < L) ? P<T>::w(I, d) : T(0);
+            pp.w[d] = (d < L) ? Prec<T>::w(I, d) : T(0);
             pp.n[d] = (d < L) ? I.lev[d].n : 0;
             pp.off[d] = I.lds_off[d];
         }
@@ -2817,7 +2948,7 @@ __global__ void __launch_bounds__(64) k_coarsest(SubArgs a)
     T* A = (T*)Lv.A;
     for (int p = threadIdx.x; p < m; p += 64) fb[p] = fs * F[(size_t)(p / n) * Lv.ldf + (p % n)];
     __syncthreads();
-    if (threadIdx.x == 0) chol_solve<T>(m, P<T>::chol(I), fb, 1, vb, 1);
+    if (threadIdx.x == 0) chol_solve<T>(m, Prec<T>::chol(I), fb, 1, vb, 1);
     __syncthreads();
     for (int p = threadIdx.x; p < m; p += 64) A[(size_t)(p / n) * Lv.lda + (p % n)] = vb[p];
 }
@@ -3152,6 +3283,26 @@ static hipError_t launch_semi(GridKernel k, const StageArgs& a, int nb, hipStrea
     return hipGetLastError();
 }
 
+// direction a.nu: 0 x-lines, 1 y-lines; points per lane a.zg (zebra_points of the launch's longest line)
+template <typename T, int DIR>
+static hipError_t launch_zebra_dir(const StageArgs& a, int nb, hipStream_t s)
+{
+    switch (a.zg) {
+    case 0: k_zebra<T, DIR, 0><<<nb, 64, 0, s>>>(a); break;
+    case 4: k_zebra<T, DIR, 4><<<nb, GRID_THREADS, 0, s>>>(a); break;
+    case 8: k_zebra<T, DIR, 8><<<nb, GRID_THREADS, 0, s>>>(a); break;
+    case 16: k_zebra<T, DIR, 16><<<nb, GRID_THREADS, 0, s>>>(a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_zebra(const StageArgs& a, int nb, hipStream_t s)
+{
+    return a.nu ? launch_zebra_dir<T, 1>(a, nb, s) : launch_zebra_dir<T, 0>(a, nb, s);
+}
+
 template <bool F32>
 static hipError_t launch_driver(GridKernel k, const StageArgs& a, int nb, hipStream_t s)
 {
@@ -3222,16 +3373,7 @@ hipError_t launch_grid(GridKernel k, bool f32, const StageArgs& a, int32_t nb, h
     case GK_PRE: e = f32 ? launch_pre<float>(a, nb, s) : launch_pre<double>(a, nb, s); break;
     case GK_POST: e = f32 ? launch_post<float>(a, nb, s) : launch_post<double>(a, nb, s); break;
     case GK_POSTPRE: e = f32 ? launch_postpre<float>(a, nb, s) : launch_postpre<double>(a, nb, s); break;
-    case GK_ZEBRA:   // direction a.nu: 0 x-lines, 1 y-lines
-        if (f32) {
-            if (a.nu) k_zebra<float, 1><<<nb, GRID_THREADS, 0, s>>>(a);
-            else k_zebra<float, 0><<<nb, GRID_THREADS, 0, s>>>(a);
-        } else {
-            if (a.nu) k_zebra<double, 1><<<nb, GRID_THREADS, 0, s>>>(a);
-            else k_zebra<double, 0><<<nb, GRID_THREADS, 0, s>>>(a);
-        }
-        e = hipGetLastError();
-        break;
+    case GK_ZEBRA: e = f32 ? launch_zebra<float>(a, nb, s) : launch_zebra<double>(a, nb, s); break;
     case GK_SWEEP: case GK_RESID: case GK_RESTRICT: case GK_ZERO: case GK_PROLONG: case GK_ADD: case GK_COPY:
     case GK_NORM: case GK_ZERO_SELF:
         if (a.semi && k != GK_NORM && k != GK_SWEEP)

@@ -236,6 +236,8 @@ struct InstLayout {
     size_t r = 0, z = 0, p = 0, q = 0;
     size_t zt64 = 0, zt32 = 0;   // zebra line-solve tables, per level [1/pivots x | multipliers x | 1/pivots y | multipliers y]
     size_t zoff[MAXL] = {};      // element offset of level d's tables
+    size_t zl64 = 0, zl32 = 0;   // the tables of levels with lines of >= ZREG_N points in the registers mapping's lane order
+    size_t zloff[MAXL] = {};
 };
 
 struct Layout {
@@ -250,18 +252,23 @@ int tiles_of(int n) { return ((n + TX - 1) / TX) * ((n + TY - 1) / TY); }
 int tiles_small(int n) { return ((n + TS - 1) / TS) * ((n + TS - 1) / TS); }
 int tiles_mid(int n) { return ((n + TM - 1) / TM) * ((n + TM - 1) / TM); }
 int tiles_tiny(int n) { return ((n + TT - 1) / TT) * ((n + TT - 1) / TT); }
-// zebra launches: the lines of one colour, ZEBRA_QUAD_LPW or two per wave on levels whose lines
-// have nx >= quad_n > 0 or nx >= wave_n > 0 points, else one per thread (64 per workgroup);
-// k_zebra takes the same decision per instance from the thresholds packed by zebra_flags
-int zebra_blocks_lines(int lines, int nx, int wave_n, int quad_n)
+int lg_of(int n)
+{
+    int lg = 0;
+    while ((1 << lg) - 1 < n) ++lg;
+    return lg;
+}
+
+// zebra launches: an instance takes the registers mapping from this line length (0: never)
+int zebra_from(const kc_exec& e) { return e.zebra_wave_n > 0 ? std::max(e.zebra_wave_n, ZREG_N) : 0; }
+// blocks of one colour's lines of one instance: GRID_THREADS threads with (nx + 1) / points lanes per
+// line, 64 at most, in the registers mapping, else one thread per line (64 per block)
+int zebra_blocks(int lines, int nx, int from, int points)
 {
     const int per_colour = (lines + 1) / 2;
-    if (!(wave_n > 0 && nx >= wave_n)) return (per_colour + 63) / 64;
-    const int per_block = (GRID_THREADS / 64) * ((quad_n > 0 && nx >= quad_n) ? ZEBRA_QUAD_LPW : 2);
+    const int per_block = from > 0 && nx >= from ? GRID_THREADS / std::min((nx + 1) / points, 64) : 64;
     return (per_colour + per_block - 1) / per_block;
 }
-int zebra_blocks(int n, int wave_n, int quad_n) { return zebra_blocks_lines(n, n, wave_n, quad_n); }
-int zebra_flags(const kc_exec& e) { return e.zebra_wave_n | (e.zebra_quad_n << 15); }
 int tiles_rect(int nx, int ny) { return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY); }
 // streaming blocks: STRIP_BLOCK_W columns x R rows, R = 16 << code; 32 rows from 2047^2 up for both
 // parts (measured faster than 16 or 64 at 8191^2 and 16383^2); the post-smoothing keeps a shape of its
@@ -334,6 +341,13 @@ kc_status make_layout(const kc_problem* probs, int count, kc_precision prec, Lay
         }
         il.zt64 = take(sizeof(double) * zt);
         il.zt32 = take(sizeof(float) * zt);
+        size_t zl = 0;   // lane-order copies, n + 1 entries per table (a multiple of 16 bytes)
+        for (int d = 0; d < il.L; ++d) {
+            il.zloff[d] = zl;
+            if (il.nx[d] >= ZREG_N) zl += 4 * (size_t)(il.nx[d] + 1);
+        }
+        il.zl64 = take(sizeof(double) * zl);
+        il.zl32 = take(sizeof(float) * zl);
         const size_t v64 = (size_t)il.n[0] * il.ld[0] * 8;
         il.r = take(v64);
         il.z = take(v64);
@@ -372,13 +386,6 @@ struct HostInst {
     int zops_beg[KMAX] = {}, zops_len[KMAX] = {};   // zebra relaxation: lists without register calls
     int lds_off[MAXL] = {}, lds_elems = 0;
 };
-
-int lg_of(int n)
-{
-    int lg = 0;
-    while ((1 << lg) - 1 < n) ++lg;
-    return lg;
-}
 
 // op list lengths / starts for a smoother (0 damped Jacobi, 1 zebra)
 const int* olen(const HostInst& hi, int smoother) { return smoother == 1 ? hi.zops_len : hi.ops_len; }
@@ -433,6 +440,7 @@ struct kc_hier {
     int max_cut = 0, max_L = 0;
     int shape[MAXL] = {};                      // StageArgs::flags of the fused grid kernels at depth d
     int shape_post[MAXL] = {};                 // the same for the post-smoothing kernel
+    int zpoints[MAXL] = {};                    // points per lane of the zebra line kernel at depth d (0: one thread per line)
     bool compacted = false;                    // the tables cover only the instances still iterating
     int last_compactions = 0;                  // table compactions during the last driver call
     int sub_lds = 0;
@@ -553,6 +561,14 @@ Launch sub(kc_hier* h, bool f32, int depth, int kappa, bool pair, int nu1, int n
     return L;
 }
 
+// the mapping of a zebra launch: points per lane (from the longest line at its depth, whatever the
+// instances still iterating) and the line length from which an instance takes the registers mapping
+void zebra_args(kc_hier* h, int d, StageArgs& a)
+{
+    a.zg = h->zpoints[d];
+    a.flags = zebra_from(h->ex) | (h->ex.zebra_quad_n << 15);
+}
+
 // fused schedule of one cycle: grid-wide PRE/POST above each instance's cut,
 // one persistent launch per parent node for the pair of calls at the cut
 void gen_fused(kc_hier* h, int d, int k, bool zg, int fin, const kc_cycle_params& c, bool f32,
@@ -622,7 +638,7 @@ void gen_paper(kc_hier* h, int d, int k, const kc_cycle_params& c, bool f32, int
         L.sa.src = cur[d];
         L.sa.dst = 0;
         L.sa.nu = 0;
-        L.sa.flags = zebra_flags(h->ex);
+        zebra_args(h, d, L.sa);
         out.push_back(L);
         return;
     }
@@ -656,7 +672,7 @@ void gen_paper(kc_hier* h, int d, int k, const kc_cycle_params& c, bool f32, int
                 L.sa.src = cur[d];
                 L.sa.dst = color;
                 L.sa.nu = h->semi ? 0 : (r & 1);   // semi-coarsening relaxes x-lines only
-                L.sa.flags = zebra_flags(h->ex);   // per instance: lines per wave from the line length
+                zebra_args(h, d, L.sa);
                 out.push_back(L);
             }
         } else {
@@ -750,11 +766,11 @@ kc_status build_tables(kc_hier* h, const std::vector<char>* active)
             const bool lvl = d < L - 1 && hi.cut > d;
             if (h->semi) {   // rectangular levels; the coarsest line is solved by the zebra kernel
                 h->tiles[tt_lvl(d)][i + 1] = lvl ? tiles_rect(hi.il.nx[d], hi.il.n[d]) : 0;
-                h->tiles[tt_zeb(d)][i + 1] = d < L ? zebra_blocks_lines(hi.il.n[d], hi.il.nx[d], h->ex.zebra_wave_n, h->ex.zebra_quad_n) : 0;
+                h->tiles[tt_zeb(d)][i + 1] = d < L ? zebra_blocks(hi.il.n[d], hi.il.nx[d], zebra_from(h->ex), h->zpoints[d]) : 0;
                 continue;
             }
             h->tiles[tt_lvl(d)][i + 1] = lvl ? tiles_of(hi.il.n[d]) : 0;
-            h->tiles[tt_zeb(d)][i + 1] = lvl ? zebra_blocks(hi.il.n[d], h->ex.zebra_wave_n, h->ex.zebra_quad_n) : 0;
+            h->tiles[tt_zeb(d)][i + 1] = lvl ? zebra_blocks(hi.il.n[d], hi.il.n[d], zebra_from(h->ex), h->zpoints[d]) : 0;
             if (hi.cut == d && d < L) h->lists[lt_sub(d)].push_back(i);
             if (L - 1 == d) h->lists[lt_coarse(d)].push_back(i);
         }
@@ -861,6 +877,10 @@ kc_status plan_exec(kc_hier* h)
         else if (maxn > 0 && maxn <= h->ex.mid_tile_n) f = 16;
         h->shape[d] = f;
         h->shape_post[d] = f;
+        int maxl = 0;   // longest line relaxed at this depth
+        for (int i = 0; i < cnt; ++i)
+            if (d < h->hi[i].il.L && (h->semi || h->hi[i].cut > d)) maxl = std::max(maxl, h->hi[i].il.nx[d]);
+        h->zpoints[d] = zebra_from(h->ex) > 0 && maxl >= zebra_from(h->ex) ? zebra_points(maxl) : 0;
     }
     kc_status st = build_tables(h, nullptr);
     if (st != KC_OK) return st;
@@ -905,6 +925,20 @@ void line_tables(int n, const double s64[9], std::vector<T>& out)
     }
 }
 
+// the last level's four tables in `lines` (n entries each) appended to `out` in the lane order of the
+// registers mapping, n + 1 entries each; the multipliers of the last point and the one past it are 0
+template <typename T>
+void lane_tables(int n, const std::vector<T>& lines, std::vector<T>& out)
+{
+    if (n < ZREG_N) return;
+    const T* src = lines.data() + lines.size() - 4 * (size_t)n;
+    const size_t base = out.size();
+    out.resize(base + 4 * (size_t)(n + 1), T(0));
+    for (int t = 0; t < 4; ++t)
+        for (int q = 0; q < ((t & 1) ? n - 1 : n); ++q)
+            out[base + (size_t)t * (n + 1) + ztab_index(n, 16 / (int)sizeof(T), q)] = src[(size_t)t * n + q];
+}
+
 void fill_inst_static(kc_hier* h)
 {
     const bool f64 = h->prec == KC_F64;
@@ -943,6 +977,8 @@ void fill_inst_static(kc_hier* h)
         for (int d = 0; d < hi.il.L; ++d) {
             I.zt64[d] = (const double*)(h->ws + hi.il.zt64) + hi.il.zoff[d];
             I.zt32[d] = (const float*)(h->ws + hi.il.zt32) + hi.il.zoff[d];
+            I.zl64[d] = (const double*)(h->ws + hi.il.zl64) + hi.il.zloff[d];
+            I.zl32[d] = (const float*)(h->ws + hi.il.zl32) + hi.il.zloff[d];
         }
         I.r = (double*)(h->ws + hi.il.r);
         I.z = (double*)(h->ws + hi.il.z);
@@ -1335,7 +1371,8 @@ std::string launch_name(const kc_hier* h, const Launch& L)
         if (L.sa.flags & 32) return k + "<" + T + ", " + nu + ", 8, 8>";
         return k + "<" + T + ", " + nu + ", 64, 32>";
     }
-    if (L.gk == GK_ZEBRA) return std::string("k_zebra<") + T + ", " + std::to_string(L.sa.nu) + ">";
+    if (L.gk == GK_ZEBRA)
+        return std::string("k_zebra<") + T + ", " + std::to_string(L.sa.nu) + ", " + std::to_string(L.sa.zg) + ">";
     if (L.gk <= GK_NORM || L.gk == GK_ZERO_SELF) return std::string("k_unfused<") + T + ", " + std::to_string(L.gk) + ">";
     return std::string("k_driver<") + (L.f32 ? "true" : "false") + ", " + std::to_string(L.gk) + ">";
     (void)h;
@@ -1590,16 +1627,21 @@ static kc_status upload_factors(kc_hier* h, int i)
     if (!coarse_cholesky<double>(hi.p.n_coarsest, hi.s[hi.il.L - 1], c64) ||
         !coarse_cholesky<float>(hi.p.n_coarsest, hi.s[hi.il.L - 1], c32))
         return fail(KC_ERR_ARG, "coarsest matrix is not positive definite");
-    std::vector<double> z64;
-    std::vector<float> z32;
+    std::vector<double> z64, l64;
+    std::vector<float> z32, l32;
     for (int d = 0; d < hi.il.L; ++d) {
         line_tables<double>(hi.il.nx[d], hi.s[d], z64);
         line_tables<float>(hi.il.nx[d], hi.s[d], z32);
+        lane_tables(hi.il.nx[d], z64, l64);
+        lane_tables(hi.il.nx[d], z32, l32);
     }
     if (hipMemcpyAsync(h->ws + hi.il.chol64, c64.data(), c64.size() * 8, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
         hipMemcpyAsync(h->ws + hi.il.chol32, c32.data(), c32.size() * 4, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
         hipMemcpyAsync(h->ws + hi.il.zt64, z64.data(), z64.size() * 8, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
         hipMemcpyAsync(h->ws + hi.il.zt32, z32.data(), z32.size() * 4, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
+        (!l64.empty() &&
+         (hipMemcpyAsync(h->ws + hi.il.zl64, l64.data(), l64.size() * 8, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
+          hipMemcpyAsync(h->ws + hi.il.zl32, l32.data(), l32.size() * 4, hipMemcpyHostToDevice, h->stream) != hipSuccess)) ||
         hipStreamSynchronize(h->stream) != hipSuccess)
         return fail(KC_ERR_HIP, "upload of the coarsest factor or the line-solve tables failed");
     return KC_OK;
