@@ -23,6 +23,8 @@ constexpr int ZREG_N = 63;        // zebra line kernel: shortest line of the reg
 inline int zebra_points(int n) { return n <= 255 ? 4 : n <= 511 ? 8 : 16; }
 // most lanes per line (log2) along direction dir (0 x, 1 y)
 __host__ __device__ inline int zebra_lg_most(int dir, bool quad) { return dir == 1 && quad ? 5 : 6; }
+constexpr int REGS_W31 = 4;         // waves of k_subtree_regs on a 31 x 31 and a 63 x 63 level
+constexpr int REGS_W63 = 8;
 constexpr int HIST_CAP = 8192;    // relres history entries kept per instance
 
 // place of point q in a table of n + 1 entries for that mapping: in order on shorter lines; from
@@ -180,6 +182,8 @@ struct SubArgs {
     int32_t fin;              // single call: FIN_STOP computes the stop test first
     int32_t wave_n;           // levels with n <= wave_n are run by one wave
     int32_t smoother;         // 0 damped Jacobi, 1 alternating zebra line relaxation
+    int32_t regs;             // size of the top level if k_subtree_regs runs the launch (every instance's, 15, 31 or 63), else 0
+    int32_t coarsest;         // its coarsest level's size (1 or 3)
     double* hist;
     // single-instance launch on an internal level (the library's own arrays): what the
     // kernel would otherwise read from the instance table before it can issue its loads

@@ -2932,6 +2932,623 @@ __global__ void __launch_bounds__(THREADS) k_subtree(SubArgs a)
     }
 }
 
+// ---------------------------------------------------------------------------
+// whole calls of damped-Jacobi cycles on a level of N x N points (N = 15, 31 or 63) of one instance,
+// coarsest level NC x NC (1 or 3), every level in registers.  k_subtree keeps the levels in LDS and
+// runs every other case (zebra, 7 x 7 coarsest levels, other sizes, lists of several sizes).
+//
+// What bounds a call is latency on one CU: a phase on 31 x 31 took 1900 cycles with the level in LDS
+// (23 LDS reads per thread of two points, 8 waves), a call on 15 x 15 9400 (3.9 us).  Here a level of
+// 31 or 63 points stays in the registers of W waves for the whole launch: lane = column, a band of U
+// consecutive rows per lane, east / west neighbours by DPP whole-wave shifts (the ring column's zeros
+// separate the bands of a wave), and per phase only a band's first and last row go through LDS to the
+// neighbouring bands, behind one barrier (two exchange buffers).  The levels from 15 down are run by
+// wave 0 alone with lane exchanges only (struct WR).  Arithmetic per point is k_subtree's.  Now a phase
+// on 31 x 31 takes about 560 cycles and a call on 15 x 15 5300; a launch of one call (kappa = 1, FP64)
+// 5.4 us instead of 12.0.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ float bperm(int addr, float x)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(x)));
+}
+__device__ __forceinline__ double bperm(int addr, double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_ds_bpermute(addr, (int)(b & 0xffffffffll));
+    const int hi = __builtin_amdgcn_ds_bpermute(addr, (int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+constexpr int DPP_ROW_SHR4 = 0x114, DPP_ROW_SHL4 = 0x104;   // values of lane - 4 / lane + 4 (0 outside the 16 lanes)
+
+// a / b, correctly rounded, from y = 1 / b (Markstein 1990: a correction with the exact remainder rounds a
+// quotient correctly once it is within a unit in the last place; the first step brings it there).  Quotients
+// whose remainder could leave the normal range are divided.
+template <typename T> __device__ __forceinline__ bool div_ok(T a)
+{
+    const T lim = sizeof(T) == 8 ? T(0x1p900) : T(0x1p100);
+    return fabs(a) > T(1) / lim && fabs(a) < lim;
+}
+template <typename T> __device__ __forceinline__ T div_fast(T a, T b, T y)
+{
+    T q = a * y;
+    q = fmadd(fmadd(-q, b, a), y, q);
+    return fmadd(fmadd(-q, b, a), y, q);
+}
+__device__ __forceinline__ float lane_of(float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); }
+__device__ __forceinline__ double lane_of(double x, int l)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// nine-point sum (three rows, south first, west to east) onto acc
+template <typename T>
+__device__ __forceinline__ T row_sum(T acc, T a, T b, T c, const Row3<T>& r)
+{
+    acc = fmadd(a, r.w, acc);
+    acc = fmadd(b, r.c, acc);
+    return fmadd(c, r.e, acc);
+}
+template <typename T> __device__ __forceinline__ Row3<T> wrow3(T v)
+{
+    return Row3<T>{dpp<DPP_WEST>(v), v, dpp<DPP_EAST>(v)};
+}
+
+// Levels 15, 7, 3 and 1 in one wave.  Level 15: lane 16 b + c holds rows 4 b .. 4 b + 3 of column c; level 7:
+// lane 8 j + i holds point (j, i); level 3: lane 4 j + i of lanes 0 - 15; level 1: lane 0.  Column and row N
+// are the zero ring.  A lane exchange that would leave the level reads a lane that holds a ring zero.
+template <typename T, int NC> struct WR {
+    T s15[9], s7[9], s3[9], w15, w7, w3;
+    clds<T> chol;                                 // coarsest factor, then the reciprocals of its diagonal
+    int nu1, nu2;
+    int lane, south15, north15, south7, north7;   // lane exchange addresses
+    int down7, down3;                             // full weighting: the fine lane of a coarse point
+    int up3[4], up7[6];                           // prolongation: coarse lanes around a fine point
+    bool col15, last15, ok7, ok3, odd7;
+
+    __device__ __forceinline__ void init(clds<T> sten, clds<T> wt, clds<T> ch, int n1, int n2)
+    {
+        lane = threadIdx.x & 63;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            s15[k] = sten[k];
+            s7[k] = sten[9 + k];
+            s3[k] = sten[18 + k];
+        }
+        w15 = wt[0];
+        w7 = wt[1];
+        w3 = wt[2];
+        chol = ch;
+        nu1 = n1;
+        nu2 = n2;
+        const int b = lane >> 4, c = lane & 15;
+        col15 = c < 15;
+        last15 = c < 15 && b < 3;              // row 4 b + 3
+        south15 = 4 * (lane >= 16 ? lane - 16 : 15);
+        north15 = 4 * (lane < 48 ? lane + 16 : 15);
+        const int j = lane >> 3, i = lane & 7;
+        ok7 = j < 7 && i < 7;
+        south7 = 4 * (lane >= 8 ? lane - 8 : 7);
+        north7 = 4 * (lane < 56 ? lane + 8 : 7);
+        down7 = 4 * (ok7 ? ((2 * j + 1) / 4) * 16 + 2 * i + 1 : 15);
+        odd7 = (j & 1) == 0;                   // fine row 2 j + 1 is row 1 (else 3) of its band
+        const int j3 = lane >> 2, i3 = lane & 3;
+        ok3 = lane < 16 && j3 < 3 && i3 < 3;
+        down3 = 4 * (ok3 ? (2 * j3 + 1) * 8 + 2 * i3 + 1 : 7);
+        const int Js = (j - 1) >> 1, Is = (i - 1) >> 1;
+        auto at3 = [&](int J, int I) { return 4 * (J < 0 || I < 0 || I > 3 || J > 3 ? 3 : J * 4 + I); };
+        up3[0] = at3(Js, Is);
+        up3[1] = at3(Js, Is + 1);
+        up3[2] = at3(Js + 1, Is);
+        up3[3] = at3(Js + 1, Is + 1);
+        const int Ic = (c - 1) >> 1;
+        auto at7 = [&](int J, int I) { return 4 * (J < 0 || I < 0 ? 7 : J * 8 + I); };
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            up7[2 * m] = at7(2 * b - 1 + m, Ic);
+            up7[2 * m + 1] = at7(2 * b - 1 + m, Ic + 1);
+        }
+    }
+
+    // level 3 (children: the 1 x 1 level, solved exactly, so a second call changes nothing)
+    __device__ __forceinline__ T sten3x(const T (&s)[9], T v) const
+    {
+        const Row3<T> S = wrow3(dpp<DPP_ROW_SHR4>(v)), C = wrow3(v), N = wrow3(dpp<DPP_ROW_SHL4>(v));
+        return row_sum(row_sum(row_sum(T(0), s[0], s[1], s[2], S), s[3], s[4], s[5], C), s[6], s[7], s[8], N);
+    }
+    __device__ __forceinline__ void call3(T& v, T f, bool zg) const
+    {
+        int q = 0;
+        if (zg) {
+            v = nu1 > 0 && ok3 ? w3 * f : T(0);
+            q = 1;
+        }
+        for (; q < nu1; ++q) {
+            const T x = fmadd(w3, f - sten3x(s3, v), v);
+            v = ok3 ? x : T(0);
+        }
+        const T res = f - sten3x(s3, v);
+        const T r = ok3 ? res : T(0);
+        const T fwc[9] = {T(0.25), T(0.5), T(0.25), T(0.5), T(1), T(0.5), T(0.25), T(0.5), T(0.25)};
+        const T fw = sten3x(fwc, r);
+        const T x = solve1(lane_of(fw, 5));
+        // the bilinear interpolant of one value: x, x / 2 or x / 4 (as sums with the ring's zeros)
+        const bool jo = ((lane >> 2) & 1) != 0, io = (lane & 1) != 0;
+        const T z = x + T(0);
+        const T e = jo && io ? x : (jo || io) ? T(0.5) * z : T(0.25) * z;
+        v = ok3 ? v + e : T(0);
+        for (q = 0; q < nu2; ++q) {
+            const T y = fmadd(w3, f - sten3x(s3, v), v);
+            v = ok3 ? y : T(0);
+        }
+    }
+    __device__ __forceinline__ T solve1(T f) const
+    {
+        const T l = chol[0], r = chol[1], y = div_fast(f, l, r);
+        if (div_ok(f) && div_ok(y)) return div_fast(y, l, r);
+        return f / l / l;
+    }
+    // the 3 x 3 level's direct solve with its Cholesky factor (9 x 9, row-major), every lane the whole of it:
+    // substitution in index order, each sum in that order
+    __device__ __forceinline__ T solve9(T f) const
+    {
+        T v[9];
+#pragma unroll
+        for (int p = 0; p < 9; ++p) v[p] = lane_of(f, p / 3 * 4 + p % 3);
+        bool ok = true;
+#pragma unroll
+        for (int p = 0; p < 9; ++p) {
+            T acc = v[p];
+#pragma unroll
+            for (int q = 0; q < p; ++q) acc -= chol[9 * p + q] * v[q];
+            ok = ok && div_ok(acc);
+            v[p] = div_fast(acc, chol[9 * p + p], chol[81 + p]);
+        }
+#pragma unroll
+        for (int p = 8; p >= 0; --p) {
+            T acc = v[p];
+#pragma unroll
+            for (int q = p + 1; q < 9; ++q) acc -= chol[9 * q + p] * v[q];
+            ok = ok && div_ok(acc);
+            v[p] = div_fast(acc, chol[9 * p + p], chol[81 + p]);
+        }
+        if (!ok) {   // a dividend outside the range above (zero included): the same with divisions
+#pragma unroll
+            for (int p = 0; p < 9; ++p) v[p] = lane_of(f, p / 3 * 4 + p % 3);
+            solve9_div(v, chol);
+        }
+        T x = v[0];
+        const int own = (lane >> 2) * 3 + (lane & 3);
+#pragma unroll
+        for (int p = 1; p < 9; ++p) x = own == p ? v[p] : x;
+        return ok3 ? x : T(0);
+    }
+    static __device__ __noinline__ void solve9_div(T (&v)[9], clds<T> L)
+    {
+#pragma unroll
+        for (int p = 0; p < 9; ++p) {
+            T acc = v[p];
+#pragma unroll
+            for (int q = 0; q < p; ++q) acc -= L[9 * p + q] * v[q];
+            v[p] = acc / L[9 * p + p];
+        }
+#pragma unroll
+        for (int p = 8; p >= 0; --p) {
+            T acc = v[p];
+#pragma unroll
+            for (int q = p + 1; q < 9; ++q) acc -= L[9 * q + p] * v[q];
+            v[p] = acc / L[9 * p + p];
+        }
+    }
+
+    __device__ __forceinline__ T sten7x(const T (&s)[9], T v) const
+    {
+        const T sv = bperm(south7, v), nv = bperm(north7, v);
+        const Row3<T> C = wrow3(v), S = wrow3(sv), N = wrow3(nv);
+        return row_sum(row_sum(row_sum(T(0), s[0], s[1], s[2], S), s[3], s[4], s[5], C), s[6], s[7], s[8], N);
+    }
+    __device__ __forceinline__ void call7(T& v, T f, int k, bool zg) const
+    {
+        int q = 0;
+        if (zg) {
+            v = nu1 > 0 && ok7 ? w7 * f : T(0);
+            q = 1;
+        }
+        for (; q < nu1; ++q) {
+            const T x = fmadd(w7, f - sten7x(s7, v), v);
+            v = ok7 ? x : T(0);
+        }
+        const T res = f - sten7x(s7, v);
+        const T r = ok7 ? res : T(0);
+        const T fwc[9] = {T(0.25), T(0.5), T(0.25), T(0.5), T(1), T(0.5), T(0.25), T(0.5), T(0.25)};
+        const T g = bperm(down3, sten7x(fwc, r));
+        const T fc = ok3 ? g : T(0);
+        T vc = T(0);
+        if constexpr (NC == 3) {
+            vc = solve9(fc);
+        } else {
+            const int calls = k > 1 ? 2 : 1;
+#pragma unroll 1
+            for (int it = 0; it < calls; ++it) call3(vc, fc, it == 0);
+        }
+        const T a = bperm(up3[0], vc), b = bperm(up3[1], vc), c = bperm(up3[2], vc), d = bperm(up3[3], vc);
+        const bool jo = ((lane >> 3) & 1) != 0, io = (lane & 1) != 0;
+        const T e = jo ? (io ? a : T(0.5) * (a + b)) : (io ? T(0.5) * (a + c) : T(0.25) * (((a + b) + c) + d));
+        v = ok7 ? v + e : T(0);
+        for (q = 0; q < nu2; ++q) {
+            const T x = fmadd(w7, f - sten7x(s7, v), v);
+            v = ok7 ? x : T(0);
+        }
+    }
+
+    // sums of the four rows of level 15; only rows 1 and 3 with `odd`.  The rows that need no other lane's
+    // band come first, while the exchanged rows are on their way
+    template <bool odd>
+    __device__ __forceinline__ void sten15(const T (&s)[9], const T (&v)[4], T (&a)[4]) const
+    {
+        const T sv = bperm(south15, v[3]), nv = bperm(north15, v[0]);
+        const Row3<T> r0 = wrow3(v[0]), r1 = wrow3(v[1]), r2 = wrow3(v[2]), r3 = wrow3(v[3]);
+        a[1] = row_sum(row_sum(row_sum(T(0), s[0], s[1], s[2], r0), s[3], s[4], s[5], r1), s[6], s[7], s[8], r2);
+        a[3] = row_sum(row_sum(T(0), s[0], s[1], s[2], r2), s[3], s[4], s[5], r3);
+        if (!odd) a[2] = row_sum(row_sum(row_sum(T(0), s[0], s[1], s[2], r1), s[3], s[4], s[5], r2), s[6], s[7], s[8], r3);
+        if (!odd) {
+            const Row3<T> S = wrow3(sv);
+            a[0] = row_sum(row_sum(row_sum(T(0), s[0], s[1], s[2], S), s[3], s[4], s[5], r0), s[6], s[7], s[8], r1);
+        }
+        const Row3<T> N = wrow3(nv);
+        a[3] = row_sum(a[3], s[6], s[7], s[8], N);
+    }
+    __device__ __forceinline__ bool ok15(int u) const { return u == 3 ? last15 : col15; }
+    __device__ __forceinline__ void sweep15(T (&v)[4], const T (&f)[4]) const
+    {
+        T a[4];
+        sten15<false>(s15, v, a);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T x = fmadd(w15, f[u] - a[u], v[u]);
+            v[u] = ok15(u) ? x : T(0);
+        }
+    }
+    __device__ __forceinline__ void call15(T (&v)[4], const T (&f)[4], int k, bool zg) const
+    {
+        int q = 0;
+        if (zg) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = nu1 > 0 && ok15(u) ? w15 * f[u] : T(0);
+            q = 1;
+        }
+        for (; q < nu1; ++q) sweep15(v, f);
+        T r[4], fw[4];
+        sten15<false>(s15, v, r);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T x = f[u] - r[u];
+            r[u] = ok15(u) ? x : T(0);
+        }
+        const T fwc[9] = {T(0.25), T(0.5), T(0.25), T(0.5), T(1), T(0.5), T(0.25), T(0.5), T(0.25)};
+        sten15<true>(fwc, r, fw);
+        const T g1 = bperm(down7, fw[1]), g3 = bperm(down7, fw[3]);
+        const T fc = ok7 ? (odd7 ? g1 : g3) : T(0);
+        T vc = T(0);
+        const int calls = k > 1 ? 2 : 1;
+#pragma unroll 1
+        for (int it = 0; it < calls; ++it) call7(vc, fc, k - it, it == 0);
+        T c[6];
+#pragma unroll
+        for (int m = 0; m < 6; ++m) c[m] = bperm(up7[m], vc);
+        const bool io = (lane & 1) != 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int m = u == 0 ? 0 : u < 3 ? 1 : 2;   // coarse row (4 b + u - 1) >> 1, counted from 2 b - 1
+            const T a0 = c[2 * m], a1 = c[2 * m + 1];
+            T e;
+            if (u & 1) {
+                e = io ? a0 : T(0.5) * (a0 + a1);
+            } else {
+                const T b0 = c[2 * m + 2], b1 = c[2 * m + 3];
+                e = io ? T(0.5) * (a0 + b0) : T(0.25) * (((a0 + a1) + b0) + b1);
+            }
+            const T x = v[u] + e;
+            v[u] = ok15(u) ? x : T(0);
+        }
+        for (q = 0; q < nu2; ++q) sweep15(v, f);
+    }
+};
+
+// LDS of the register kernel
+template <typename T, int N, int W> struct RegsLds {
+    static constexpr int NB31 = W * 2;
+    T ex63[N == 63 ? 2 : 1][2][N == 63 ? W + 2 : 1][64];   // exchanged rows: [buffer][first / last][band + 1][column]
+    T ex31[2][2][NB31 + 2][32];
+    T f31[N == 63 ? 32 : 1][32], v31[N == 63 ? 33 : 1][33];   // right-hand side of level 31; its solution with a zero ring
+    T f15[16][16], v15[17][17];
+    T s[6][9], w[6], chol[90];
+    double red[2 * W];
+    int stop;
+};
+
+// a level of M x M points (31 or 63) in the registers of W waves
+template <typename T, int M, int W> struct BL {
+    static constexpr int B = M + 1, BPW = 64 / B, NB = W * BPW, U = B / NB;
+    static_assert(U >= 2 && U % 2 == 0, "a band starts at an even row");
+    T s[9], w;
+    T (*ex)[2][NB + 2][B];   // [2]
+    int band, c, buf;
+    bool col;
+
+    __device__ __forceinline__ void init(T (*e)[2][NB + 2][B], clds<T> sten, T wt)
+    {
+        ex = e;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) s[k] = lane_of(sten[k], 0);   // scalar registers: the level's rows need the others
+        w = lane_of(wt, 0);
+        c = threadIdx.x & (B - 1);
+        band = threadIdx.x / B;
+        buf = 0;
+        col = c < M;
+    }
+    __device__ __forceinline__ bool ok(int u) const { return u == U - 1 ? col && band < NB - 1 : col; }
+    // the bands' first and last rows of v to the neighbouring bands: S (row -1) and N (row U) of this one
+    __device__ __forceinline__ void exchange(const T (&v)[U], T& S, T& N)
+    {
+        buf ^= 1;
+        ex[buf][0][band + 1][c] = v[0];
+        ex[buf][1][band + 1][c] = v[U - 1];
+        __syncthreads();
+        S = ex[buf][1][band][c];
+        N = ex[buf][0][band + 2][c];
+    }
+    __device__ __forceinline__ void sums(const T (&v)[U], T (&a)[U])
+    {
+        T S, N;
+        exchange(v, S, N);
+        Row3<T> r[U + 2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u + 1] = row3(v[u]);
+        r[0] = row3(S);
+        r[U + 1] = row3(N);
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = T(0);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[u] = fmadd(s[3 * b], r[u + b].w, a[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[u] = fmadd(s[3 * b + 1], r[u + b].c, a[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[u] = fmadd(s[3 * b + 2], r[u + b].e, a[u]);
+        }
+    }
+    __device__ __forceinline__ void sweep(T (&v)[U], const T (&f)[U])
+    {
+        T a[U];
+        sums(v, a);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const T x = fmadd(w, f[u] - a[u], v[u]);
+            v[u] = ok(u) ? x : T(0);
+        }
+    }
+    // nu sweeps, residual and full weighting into Fc
+    template <int CB>
+    __device__ __forceinline__ void pre(T (&v)[U], const T (&f)[U], int nu, bool zg, T (*Fc)[CB])
+    {
+        int q = 0;
+        if (zg) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = nu > 0 && ok(u) ? w * f[u] : T(0);
+            q = 1;
+        }
+#pragma unroll 1
+        for (; q < nu; ++q) sweep(v, f);
+        T r[U + 1], a[U], S;
+        sums(v, a);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const T x = f[u] - a[u];
+            a[u] = ok(u) ? x : T(0);
+            r[u] = a[u];
+        }
+        exchange(a, S, r[U]);
+        const T h = T(0.5), g = T(0.25);
+#pragma unroll
+        for (int u = 1; u < U; u += 2) {
+            const Row3<T> s0 = row3(r[u - 1]), s1 = row3(r[u]), s2 = row3(r[u + 1]);
+            T acc = row_sum(row_sum(row_sum(T(0), g, h, g, s0), h, T(1), h, s1), g, h, g, s2);
+            const int J = (band * U + u - 1) / 2;
+            if ((c & 1) && J < (M - 1) / 2) Fc[J][(c - 1) / 2] = acc;
+        }
+        __syncthreads();
+    }
+    // prolongation of Vc (zero ring) added, nu sweeps
+    template <int CP>
+    __device__ __forceinline__ void post(T (&v)[U], const T (&f)[U], int nu, const T (*Vc)[CP])
+    {
+        const int I = (c - 1) >> 1, J0 = band * (U / 2) - 1;   // coarse row (band U - 1) >> 1
+        const bool io = (c & 1) != 0;
+        T a[U / 2 + 1], b[U / 2 + 1];
+#pragma unroll
+        for (int m = 0; m <= U / 2; ++m) {
+            a[m] = Vc[J0 + m + 1][I + 1];
+            b[m] = Vc[J0 + m + 1][min(I + 2, CP - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int m = (u + 1) / 2;
+            T e;
+            if (u & 1) e = io ? a[m] : T(0.5) * (a[m] + b[m]);
+            else e = io ? T(0.5) * (a[m] + a[m + 1]) : T(0.25) * (((a[m] + b[m]) + a[m + 1]) + b[m + 1]);
+            const T x = v[u] + e;
+            v[u] = ok(u) ? x : T(0);
+        }
+#pragma unroll 1
+        for (int q = 0; q < nu; ++q) sweep(v, f);
+    }
+};
+
+template <typename T, int N, int W, int NC>
+__global__ void __launch_bounds__(64 * W) k_subtree_regs(SubArgs a)
+{
+    static_assert((N == 15 || N == 31 || N == 63) && (NC == 1 || NC == 3), "levels");
+    __shared__ RegsLds<T, N, W> L;
+    const int inst = (a.count == 1) ? a.first : a.list[blockIdx.x];
+    const InstDev& I = a.inst[inst];
+    const int done = a.st[inst].done;
+    const int d0 = a.depth;
+    const bool fast = a.ops1 != nullptr;
+    const LevelDev& Lv = I.lev[d0];
+    const T fs = (T)(fast ? a.fs0 : Lv.fscale);
+    const gp<const T> Fg = glob<T>(fast ? a.F0 : (const void*)Lv.F);
+    const gp<T> Ag = glob<T>(fast ? a.A0 : Lv.A);
+    const int ldf = fast ? a.ldf0 : Lv.ldf, lda = fast ? a.lda0 : Lv.lda;
+    const bool zero = a.pair || a.zg;
+
+    // the top level's rows of this lane (clamped addresses, masked below)
+    constexpr int B = N + 1, U = N == 15 ? 4 : B / (W * (64 / B));
+    const int tid = threadIdx.x, c = tid & (B - 1), row = (tid / B) * U;
+    T f[U], v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const size_t j = min(row + u, N - 1), i = min(c, N - 1);
+        f[u] = Fg[j * ldf + i];
+        v[u] = zero ? T(0) : Ag[j * lda + i];
+    }
+    // stencils and weights of the levels, the coarsest factor, zeros of rings and guard rows
+    constexpr int NL = N == 63 ? 5 : N == 31 ? 4 : 3;   // relaxed levels
+    if (tid < NL * 9) L.s[tid / 9][tid % 9] = Prec<T>::s(I, d0)[tid];
+    if (W == 1 ? tid < NL : tid >= 64 * (W - 1) && tid < 64 * (W - 1) + NL) L.w[tid & 63] = Prec<T>::w(I, d0 + (tid & 63));
+    const T* const ch = fast ? (const T*)a.chol0 : Prec<T>::chol(I);
+    if constexpr (NC == 1) {
+        if (tid == 64 * W - 1) {
+            const T l = ch[0];
+            L.chol[0] = l;
+            L.chol[1] = T(1) / l;
+        }
+    } else {
+        for (int p = tid; p < 81; p += 64 * W) {
+            const T l = ch[p];
+            L.chol[p] = l;
+            if (p % 10 == 0) L.chol[81 + p / 10] = T(1) / l;
+        }
+    }
+    if constexpr (N == 63)
+        for (int p = tid; p < 33 * 33; p += 64 * W) (&L.v31[0][0])[p] = T(0);
+    if constexpr (N >= 31) {
+        for (int p = tid; p < 17 * 17; p += 64 * W) (&L.v15[0][0])[p] = T(0);
+        for (int p = tid; p < 2 * 2 * 32; p += 64 * W) L.ex31[p >> 6][1 - ((p >> 5) & 1)][(p >> 5) & 1 ? 2 * W + 1 : 0][p & 31] = T(0);
+    }
+    if constexpr (N == 63)
+        for (int p = tid; p < 2 * 2 * 64; p += 64 * W) L.ex63[p >> 7][1 - ((p >> 6) & 1)][(p >> 6) & 1 ? W + 1 : 0][p & 63] = T(0);
+    if (done) return;   // the whole workgroup leaves together
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool in = c < N && row + u < N;
+        f[u] = in ? fs * f[u] : T(0);
+        v[u] = in ? v[u] : T(0);
+    }
+    __syncthreads();
+
+    BL<T, 63, N == 63 ? W : 8> l63;
+    BL<T, 31, N >= 31 ? W : 4> l31;
+    WR<T, NC> wr;
+    constexpr int r31 = N == 63 ? 1 : 0, r15 = NL - 3;
+    if constexpr (N == 63) l63.init(L.ex63, to_lds<T>((const T*)&L.s[0][0]), L.w[0]);
+    if constexpr (N >= 31) l31.init(L.ex31, to_lds<T>((const T*)&L.s[r31][0]), L.w[r31]);
+    const bool w0 = tid < 64;
+    auto init15 = [&] {
+        wr.init(to_lds<T>((const T*)&L.s[r15][0]), to_lds<T>((const T*)&L.w[r15]), to_lds<T>((const T*)&L.chol[0]), a.nu1, a.nu2);
+    };
+    if (N != 63 && w0) init15();
+
+    if (a.fin == FIN_STOP) {   // stop test on the input residual (a solve whose fine level is this one)
+        T r[U];
+        if constexpr (N == 63) l63.sums(v, r);
+        else if constexpr (N == 31) l31.sums(v, r);
+        else wr.template sten15<false>(wr.s15, v, r);
+        Acc2 nrm;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c < N && row + u < N) nrm.add_sq((double)(f[u] - r[u]));
+        wave_merge(nrm);
+        if ((tid & 63) == 0) {
+            L.red[2 * (tid >> 6)] = nrm.s;
+            L.red[2 * (tid >> 6) + 1] = nrm.c;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            Acc2 ss;
+            for (int k = 0; k < W; ++k) ss.merge(L.red[2 * k], L.red[2 * k + 1]);
+            stop_test(a.st[inst], a.hist, inst, ss.value());
+            L.stop = a.st[inst].done;
+        }
+        __syncthreads();
+        if (L.stop) return;
+    }
+
+    // calls on level 15 with counters k and, for k > 1, k - 1: right-hand side from L.f15, result to L.v15
+    auto pair15 = [&](int k) {
+        if (w0) {
+            if (N == 63) init15();   // not kept over the phases of level 63, which need the registers
+            const int b = wr.lane >> 4, cc = wr.lane & 15;
+            T fc[4], vc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const T x = L.f15[4 * b + u][cc];
+                fc[u] = wr.ok15(u) ? x : T(0);
+                vc[u] = T(0);
+            }
+            const int calls = k > 1 ? 2 : 1;
+#pragma unroll 1
+            for (int it = 0; it < calls; ++it) wr.call15(vc, fc, k - it, it == 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (wr.ok15(u)) L.v15[4 * b + u + 1][cc + 1] = vc[u];
+        }
+        __syncthreads();
+    };
+    const int calls = a.pair && a.kappa > 1 ? 2 : 1;
+    if constexpr (N == 15) {
+#pragma unroll 1
+        for (int it = 0; it < calls; ++it) wr.call15(v, f, a.kappa - it, zero && it == 0);
+    } else if constexpr (N == 31) {
+#pragma unroll 1
+        for (int it = 0; it < calls; ++it) {
+            l31.pre(v, f, a.nu1, zero && it == 0, L.f15);
+            pair15(a.kappa - it);
+            l31.post(v, f, a.nu2, L.v15);
+        }
+    } else {
+#pragma unroll 1
+        for (int it = 0; it < calls; ++it) {
+            l63.pre(v, f, a.nu1, zero && it == 0, L.f31);
+            const int k = a.kappa - it, calls31 = k > 1 ? 2 : 1;
+            constexpr int U31 = BL<T, 31, W>::U;
+            T f31[U31], v31[U31];
+#pragma unroll
+            for (int u = 0; u < U31; ++u) {
+                const T x = L.f31[l31.band * U31 + u][l31.c];
+                f31[u] = l31.ok(u) ? x : T(0);
+                v31[u] = T(0);
+            }
+#pragma unroll 1
+            for (int jt = 0; jt < calls31; ++jt) {
+                l31.pre(v31, f31, a.nu1, jt == 0, L.f15);
+                pair15(k - jt);
+                l31.post(v31, f31, a.nu2, L.v15);
+            }
+#pragma unroll
+            for (int u = 0; u < U31; ++u)
+                if (l31.ok(u)) L.v31[l31.band * U31 + u + 1][l31.c + 1] = v31[u];
+            __syncthreads();
+            l63.post(v, f, a.nu2, L.v31);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (c < N && row + u < N) Ag[(size_t)(row + u) * lda + c] = v[u];
+}
+
 // coarsest direct solve on global memory (paper-structured mode); the coarsest
 // grid is at most 7 x 7, staged through LDS
 template <typename T>
@@ -3389,9 +4006,23 @@ hipError_t launch_grid(GridKernel k, bool f32, const StageArgs& a, int32_t nb, h
     return launch_finalize(a, s);
 }
 
+template <typename T, int NC>
+static hipError_t launch_regs(const SubArgs& a, hipStream_t s)
+{
+    switch (a.regs) {
+    case 15: k_subtree_regs<T, 15, 1, NC><<<a.count, 64, 0, s>>>(a); break;
+    case 31: k_subtree_regs<T, 31, REGS_W31, NC><<<a.count, 64 * REGS_W31, 0, s>>>(a); break;
+    case 63: k_subtree_regs<T, 63, REGS_W63, NC><<<a.count, 64 * REGS_W63, 0, s>>>(a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_subtree(bool f32, const SubArgs& a, int32_t threads, int32_t lds_bytes, hipStream_t s)
 {
     if (a.count <= 0) return hipSuccess;
+    if (a.regs && a.coarsest == 1) return f32 ? launch_regs<float, 1>(a, s) : launch_regs<double, 1>(a, s);
+    if (a.regs && a.coarsest == 3) return f32 ? launch_regs<float, 3>(a, s) : launch_regs<double, 3>(a, s);
     const bool z = a.smoother == 1;
     if (threads == 256) {
         if (f32) z ? k_subtree<float, 256, true><<<a.count, 256, lds_bytes, s>>>(a)

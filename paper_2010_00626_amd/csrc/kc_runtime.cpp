@@ -512,6 +512,21 @@ Launch fused_grid(kc_hier* h, GridKernel gk, bool f32, int d)
     return L;
 }
 
+// whether the register kernel runs the calls at this depth (damped Jacobi down to a 1 x 1 or 3 x 3 level,
+// instances of one size): sets the launch's level sizes, else k_subtree runs them
+void set_regs(const kc_hier* h, int depth, int smoother, SubArgs& a)
+{
+    a.regs = a.coarsest = 0;
+    if (smoother != 0 || !h->ex.wave_regs || h->ex.coarse_wave_n != 15 || h->lists[lt_sub(depth)].empty()) return;
+    const HostInst& first = h->hi[h->lists[lt_sub(depth)][0]];
+    const int n = first.il.n[depth], nc = first.p.n_coarsest;
+    if ((n != 15 && n != 31 && n != 63) || (nc != 1 && nc != 3)) return;
+    for (int i : h->lists[lt_sub(depth)])
+        if (h->hi[i].p.n_coarsest != nc || h->hi[i].il.n[depth] != n) return;
+    a.regs = n;
+    a.coarsest = nc;
+}
+
 Launch sub(kc_hier* h, bool f32, int depth, int kappa, bool pair, int nu1, int nu2, bool zg, int fin, int smoother = 0)
 {
     Launch L{};
@@ -534,6 +549,7 @@ Launch sub(kc_hier* h, bool f32, int depth, int kappa, bool pair, int nu1, int n
     L.ba.hist = h->d_hist;
     L.threads = h->ex.coarse_threads;
     L.lds = smoother == 1 ? h->sub_lds_z : h->sub_lds;
+    set_regs(h, depth, smoother, L.ba);
     if (L.ba.count == 1 && depth > 0 && h->h_inst && h->ws) {
         // one instance on an internal level: its tables are fixed for the plan, so the
         // launch carries them and the kernel issues every load in one round
@@ -1356,6 +1372,9 @@ constexpr double FL_PROLONG = 3.0;    // average over injected, edge and centre 
 std::string launch_name(const kc_hier* h, const Launch& L)
 {
     const char* T = L.f32 ? "float" : "double";
+    if (L.type == L_SUB && L.ba.regs)
+        return std::string("k_subtree_regs<") + T + ", " + std::to_string(L.ba.regs) + ", " +
+               std::to_string(L.ba.regs == 63 ? REGS_W63 : L.ba.regs == 31 ? REGS_W31 : 1) + ", " + std::to_string(L.ba.coarsest) + ">";
     if (L.type == L_SUB)
         return std::string("k_subtree<") + T + ", " + std::to_string(L.threads) + (L.ba.smoother == 1 ? ", true>" : ", false>");
     if (L.type == L_COARSEST) return std::string("k_coarsest<") + T + ">";
