@@ -198,7 +198,7 @@ template <int CTRL> __device__ __forceinline__ double dpp(double x)
 constexpr int DPP_WAVE_SHR1 = 0x138;   // wave_shr:1 -> value of lane - 1 (0 in lane 0)
 constexpr int DPP_WAVE_SHL1 = 0x130;   // wave_shl:1 -> value of lane + 1 (0 in lane 63)
 struct Tile {
-    int inst, blk, nblk, x0, y0;
+    int inst, blk, x0, y0;
 };
 
 __device__ inline int find_inst(const int32_t* off, int count, int b)
@@ -211,21 +211,40 @@ __device__ inline int find_inst(const int32_t* off, int count, int b)
     return lo;
 }
 
-// returns false when the instance is finished (the whole block leaves together)
-template <int BX = TX, int BY = TY>
-__device__ inline bool get_tile(const StageArgs& a, int depth_for_size, bool fine_user, Tile& t)
+// the block's instance, its place among the instance's blocks and their number; false when the
+// instance is finished (the whole block leaves together).  A launch of a small level takes about
+// 2 us on the CU, of which loads that wait for one another were a third, so a hierarchy of one
+// instance reads no block table here and its kernels check the stop flag (finished) once the loads
+// of their data are in flight: every address follows from the kernel's arguments and one round of
+// scalar loads.
+__device__ __forceinline__ bool block_of(const StageArgs& a, int& inst, int& blk, int& nblk)
 {
-    const int b = blockIdx.x;
-    const int i = find_inst(a.tile_off, a.count, b);
-    t.inst = i;
-    t.blk = b - a.tile_off[i];
-    t.nblk = a.tile_off[i + 1] - a.tile_off[i];
-    const InstDev& I = a.inst[i];
-    const int n = fine_user ? I.n0 : I.lev[depth_for_size].n;
-    const int tx = (n + BX - 1) / BX;
-    t.x0 = (t.blk % tx) * BX;
-    t.y0 = (t.blk / tx) * BY;
-    return a.st[i].done == 0;
+    inst = 0;
+    blk = blockIdx.x;
+    nblk = gridDim.x;
+    if (a.count > 1) {
+        inst = find_inst(a.tile_off, a.count, blk);
+        const int first = a.tile_off[inst];
+        nblk = a.tile_off[inst + 1] - first;
+        blk -= first;
+        return a.st[inst].done == 0;
+    }
+    return true;
+}
+// stop flag read with the first round of loads and looked at here: loads before this point stay before it
+__device__ __forceinline__ bool finished(int done)
+{
+    asm volatile("" : "+s"(done) : : "memory");
+    return done != 0;
+}
+
+// tile of a level of n points a side (n + 1 a power of two, so the tiles of a row are too)
+template <int BX = TX, int BY = TY>
+__device__ __forceinline__ Tile tile_at(int inst, int blk, int n)
+{
+    static_assert((BX & (BX - 1)) == 0, "tile width");
+    const int lgx = max(31 - __clz(n + 1) - __builtin_ctz(BX), 0);
+    return Tile{inst, blk, (blk & ((1 << lgx) - 1)) * BX, (blk >> lgx) * BY};
 }
 
 // Norms and dot products are Dot2 sums (Ogita, Rump and Oishi, "Accurate sum
@@ -410,7 +429,7 @@ __device__ void reduce_partial(const StageArgs& a, const Tile& t, const Acc2& v0
     const Acc2 s0 = block_sum<GRID_THREADS>(v0, red[0]);
     const Acc2 s1 = block_sum<GRID_THREADS>(v1, red[1]);
     if (threadIdx.x == 0) {
-        const int gb = a.tile_off[t.inst] + t.blk;
+        const int gb = blockIdx.x;
         a.partial[4 * gb] = s0.s;
         a.partial[4 * gb + 1] = s0.c;
         a.partial[4 * gb + 2] = s1.s;
@@ -454,18 +473,21 @@ template <typename T> __device__ inline T* buf(const LevelDev& L, int sel) { ret
 template <typename T, int kind>
 __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
 {
-    Tile t;
-    if (!get_tile(a, a.depth, false, t)) return;
-    const InstDev& I = a.inst[t.inst];
+    int inst, blk, nblk;
+    if (!block_of(a, inst, blk, nblk)) return;
+    const InstDev& I = a.inst[inst];
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const int n = Lv.n;
+    const Tile t = tile_at(inst, blk, n);
+    const int done = a.st[inst].done;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     Sten<T> s;
     s.load(Prec<T>::s(I, d));
     const T w = Prec<T>::w(I, d);
     const T fs = (T)Lv.fscale;
     const T* F = (const T*)Lv.F;
+    if (finished(done)) return;
     Acc2 nrm;
     const int lds_ = a.src ? Lv.ldb : Lv.lda;   // leading dimension of the source buffer
     const int ldd_ = a.dst ? Lv.ldb : Lv.lda;   // leading dimension of the destination buffer
@@ -578,14 +600,14 @@ __device__ inline T sload(const T* p, int ld, int ny, int nx, int j, int i)
 template <typename T, int kind>
 __global__ void __launch_bounds__(GRID_THREADS) k_semi(StageArgs a)
 {
-    const int b = blockIdx.x;
-    const int inst = find_inst(a.tile_off, a.count, b);
-    if (a.st[inst].done) return;
+    int inst, blk, nblk;
+    if (!block_of(a, inst, blk, nblk)) return;
+    const int done = a.st[inst].done;
     const InstDev& I = a.inst[inst];
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const int ny = Lv.n, nx = Lv.nx;
-    const int blk = b - a.tile_off[inst];
+    if (finished(done)) return;
     const int tiles_x = (nx + TX - 1) / TX;
     const int x0 = (blk % tiles_x) * TX, y0 = (blk / tiles_x) * TY;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -1093,20 +1115,20 @@ __device__ __forceinline__ void zebra_regs(const ZRegs<T, DIR, P>& z)
 template <typename T, int DIR, int P>
 __global__ void __launch_bounds__(GRID_THREADS) k_zebra(StageArgs a)
 {
-    const int b = blockIdx.x;
-    const int inst = find_inst(a.tile_off, a.count, b);
-    if (a.st[inst].done) return;
+    int inst, blk, nblk;
+    if (!block_of(a, inst, blk, nblk)) return;
+    const int done = a.st[inst].done;
     const InstDev& I = a.inst[inst];
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const int n = Lv.n, nx = Lv.nx;   // lines and points per line (equal except on semi-coarsened levels)
-    const int toff = a.tile_off[inst];
-    int blk = b - toff;
+    const int toff = blockIdx.x - blk;
     Sten<T> s;
     s.load(Prec<T>::s(I, d));
     const gp<T> V = glob<T>(buf<T>(Lv, a.src));
     const gp<const T> F = glob<T>((const void*)Lv.F);
     const int ldv = a.src ? Lv.ldb : Lv.lda;   // element offsets fit 32 bits (n <= 2^14)
+    if (finished(done)) return;
     if constexpr (P > 0) {
         // flags: bits 0-14 the line length from which an instance takes the registers mapping (0 never),
         // bits 15-29 that from which its y-lines take half as many lanes (0 never)
@@ -1263,12 +1285,14 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     constexpr int RW = TX + 2 * H + 1, RH = TY + 2 * H + 1;
     __shared__ T sv[2][RH * RW];
     __shared__ T sf[RH * RW];
-    Tile t;
-    if (!get_tile<TX, TY>(a, a.depth, false, t)) return;
-    const InstDev& I = a.inst[t.inst];
+    int inst, blk, nblk;
+    if (!block_of(a, inst, blk, nblk)) return;
+    const InstDev& I = a.inst[inst];
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const int n = Lv.n;
+    const Tile t = tile_at<TX, TY>(inst, blk, n);
+    const int done = a.st[inst].done;
     const gp<const T> A = glob<T>((const void*)Lv.A);
     const gp<T> B = glob<T>(Lv.B);
     const gp<const T> F = glob<T>((const void*)Lv.F);
@@ -1280,7 +1304,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     const bool zg = a.zg != 0;
     // a zero guess reads no estimate: F, with its own leading dimension, is a valid stand-in address
     const gp<const T> Av = zg ? F : A;
-    const size_t ldav = zg ? (size_t)Lv.ldf : (size_t)Lv.lda;
+    const size_t ldav = (size_t)(Lv.lda + (int)zg * (Lv.ldf - Lv.lda));   // both read at once
 
     {   // every load of the region in flight before the LDS stores
         constexpr int NR = RH * RW, NPT = (NR + GRID_THREADS - 1) / GRID_THREADS;
@@ -1297,6 +1321,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
             fa[k] = in ? fs * lf : T(0);
             va[k] = (in && !zg) ? lv : T(0);
         }
+        if (finished(done)) return;
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             const int p = threadIdx.x + k * GRID_THREADS;
@@ -1386,12 +1411,14 @@ __global__ void __launch_bounds__(GRID_THREADS) k_post(StageArgs a)
     __shared__ T sv[2][RH * RW];
     __shared__ T sf[RH * RW];
     __shared__ T sc[CH * CW];
-    Tile t;
-    if (!get_tile<TX, TY>(a, a.depth, false, t)) return;
-    const InstDev& I = a.inst[t.inst];
+    int inst, blk, nblk;
+    if (!block_of(a, inst, blk, nblk)) return;
+    const InstDev& I = a.inst[inst];
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const LevelDev& Lc = I.lev[d + 1];
+    const Tile t = tile_at<TX, TY>(inst, blk, Lv.n);
+    const int done = a.st[inst].done;
     const int n = Lv.n, nc = Lc.n, ldc = Lc.lda;
     const gp<T> A = glob<T>(Lv.A);
     const gp<const T> B = glob<T>((const void*)Lv.B);
@@ -1427,6 +1454,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_post(StageArgs a)
             const T cv = gload(Vc, ldc, nc, cy0 + cj, cx0 + ci);
             ca[k] = (p < NC) ? cv : T(0);
         }
+        if (finished(done)) return;
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             const int p = threadIdx.x + k * GRID_THREADS;
@@ -1495,12 +1523,14 @@ __global__ void __launch_bounds__(GRID_THREADS) k_postpre(StageArgs a)
     __shared__ T sv[2][RH * RW];
     __shared__ T sf[RH * RW];
     __shared__ T sc[CH * CW];
-    Tile t;
-    if (!get_tile<TX, TY>(a, a.depth, false, t)) return;
-    const InstDev& I = a.inst[t.inst];
+    int inst, blk, nblk;
+    if (!block_of(a, inst, blk, nblk)) return;
+    const InstDev& I = a.inst[inst];
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const LevelDev& Lc = I.lev[d + 1];
+    const Tile t = tile_at<TX, TY>(inst, blk, Lv.n);
+    const int done = a.st[inst].done;
     const int n = Lv.n, nc = Lc.n;
     const gp<T> B = glob<T>(Lv.B);
     const gp<const T> F = glob<T>((const void*)Lv.F);
@@ -1536,6 +1566,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_postpre(StageArgs a)
             const T cv = gload(Vc, Lc.lda, nc, cy0 + cj, cx0 + ci);
             ca[k] = (p < NC) ? cv : T(0);
         }
+        if (finished(done)) return;
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             const int p = threadIdx.x + k * GRID_THREADS;
@@ -1685,24 +1716,19 @@ struct Strip {
 template <int R>
 __device__ inline bool get_strip(const StageArgs& a, Strip& t)
 {
-    const int b = blockIdx.x;
-    const int i = find_inst(a.tile_off, a.count, b);
-    t.inst = i;
-    t.blk = b - a.tile_off[i];   // the block's partial-sum slot
-    const int n = a.inst[i].lev[a.depth].n;
+    int blk, nb;
+    if (!block_of(a, t.inst, blk, nb)) return false;
+    t.blk = blk;   // the block's partial-sum slot
+    const int n = a.inst[t.inst].lev[a.depth].n;
     const int nbx = (n + STRIP_BLOCK_W - 1) / STRIP_BLOCK_W;
     // workgroups go round-robin over the eight XCDs: give each XCD a contiguous run of
     // strips (whole bands of rows), so that the halo rows and columns neighbouring strips
     // share are read through one L2
-    int blk = t.blk;
-    {
-        const int nb = a.tile_off[i + 1] - a.tile_off[i];
-        if ((a.tile_off[i] & 7) == 0 && (nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
-    }
+    if (((blockIdx.x - blk) & 7) == 0 && (nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
     t.x0 = ((blk % nbx) * SWAVES + (int)(threadIdx.x >> 6)) * SW;
     t.y0 = (blk / nbx) * R;
     t.live = t.x0 < n;
-    return a.st[i].done == 0;
+    return a.st[t.inst].done == 0;
 }
 
 // A stage's nine-point sums in rolling form: when the stage above delivers a
@@ -3611,11 +3637,12 @@ struct DWin {
 template <bool F32, int kind>
 __global__ void __launch_bounds__(GRID_THREADS) k_driver(StageArgs a)
 {
-    Tile t;
-    if (!get_tile(a, 0, true, t)) return;
-    const InstDev& I = a.inst[t.inst];
-    InstState& st = a.st[t.inst];
+    int inst, blk, nblk;
+    if (!block_of(a, inst, blk, nblk) || a.st[inst].done) return;
+    const InstDev& I = a.inst[inst];
+    InstState& st = a.st[inst];
     const int n = I.n0;
+    const Tile t = tile_at(inst, blk, n);
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int i = t.x0 + tx, jb = t.y0 + ty * DR;
     const int ic = clampi(i, n);

@@ -1646,22 +1646,24 @@ static kc_status upload_factors(kc_hier* h, int i)
     if (!coarse_cholesky<double>(hi.p.n_coarsest, hi.s[hi.il.L - 1], c64) ||
         !coarse_cholesky<float>(hi.p.n_coarsest, hi.s[hi.il.L - 1], c32))
         return fail(KC_ERR_ARG, "coarsest matrix is not positive definite");
+    // line-solve tables in the precision of the hierarchy's cycles
     std::vector<double> z64, l64;
     std::vector<float> z32, l32;
+    const bool f64 = h->prec == KC_F64;
     for (int d = 0; d < hi.il.L; ++d) {
-        line_tables<double>(hi.il.nx[d], hi.s[d], z64);
-        line_tables<float>(hi.il.nx[d], hi.s[d], z32);
-        lane_tables(hi.il.nx[d], z64, l64);
-        lane_tables(hi.il.nx[d], z32, l32);
+        if (f64) {
+            line_tables<double>(hi.il.nx[d], hi.s[d], z64);
+            lane_tables(hi.il.nx[d], z64, l64);
+        } else {
+            line_tables<float>(hi.il.nx[d], hi.s[d], z32);
+            lane_tables(hi.il.nx[d], z32, l32);
+        }
     }
-    if (hipMemcpyAsync(h->ws + hi.il.chol64, c64.data(), c64.size() * 8, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        hipMemcpyAsync(h->ws + hi.il.chol32, c32.data(), c32.size() * 4, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        hipMemcpyAsync(h->ws + hi.il.zt64, z64.data(), z64.size() * 8, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        hipMemcpyAsync(h->ws + hi.il.zt32, z32.data(), z32.size() * 4, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        (!l64.empty() &&
-         (hipMemcpyAsync(h->ws + hi.il.zl64, l64.data(), l64.size() * 8, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-          hipMemcpyAsync(h->ws + hi.il.zl32, l32.data(), l32.size() * 4, hipMemcpyHostToDevice, h->stream) != hipSuccess)) ||
-        hipStreamSynchronize(h->stream) != hipSuccess)
+    auto put = [&](size_t at, const auto& v) {
+        return v.empty() || hipMemcpyAsync(h->ws + at, v.data(), v.size() * sizeof v[0], hipMemcpyHostToDevice, h->stream) == hipSuccess;
+    };
+    if (!put(hi.il.chol64, c64) || !put(hi.il.chol32, c32) || !put(hi.il.zt64, z64) || !put(hi.il.zt32, z32) ||
+        !put(hi.il.zl64, l64) || !put(hi.il.zl32, l32) || hipStreamSynchronize(h->stream) != hipSuccess)
         return fail(KC_ERR_HIP, "upload of the coarsest factor or the line-solve tables failed");
     return KC_OK;
 }
