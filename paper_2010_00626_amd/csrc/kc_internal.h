@@ -23,8 +23,9 @@ constexpr int ZREG_N = 63;        // zebra line kernel: shortest line of the reg
 inline int zebra_points(int n) { return n <= 255 ? 4 : n <= 511 ? 8 : 16; }
 // most lanes per line (log2) along direction dir (0 x, 1 y)
 __host__ __device__ inline int zebra_lg_most(int dir, bool quad) { return dir == 1 && quad ? 5 : 6; }
-constexpr int REGS_W31 = 4;         // waves of k_subtree_regs on a 31 x 31 and a 63 x 63 level
-constexpr int REGS_W63 = 8;
+// waves of k_subtree_regs on a top level of n points a side.  63: eight (kappa = 1: 13.6 us against 14.3
+// with four), but four in FP64 above a 3 x 3 coarsest level, whose solve eight waves' registers do not hold
+constexpr int regs_waves(int n, bool f64, int nc) { return n == 15 ? 1 : n == 31 || (f64 && nc == 3) ? 4 : 8; }
 constexpr int HIST_CAP = 8192;    // relres history entries kept per instance
 
 // place of point q in a table of n + 1 entries for that mapping: in order on shorter lines; from

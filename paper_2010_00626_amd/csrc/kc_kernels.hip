@@ -3027,13 +3027,14 @@ template <typename T> __device__ __forceinline__ Row3<T> wrow3(T v)
 template <typename T, int NC> struct WR {
     T s15[9], s7[9], s3[9], w15, w7, w3;
     clds<T> chol;                                 // coarsest factor, then the reciprocals of its diagonal
+    lds<T> tmp;                                   // 9 elements (3 x 3 coarsest level)
     int nu1, nu2;
     int lane, south15, north15, south7, north7;   // lane exchange addresses
     int down7, down3;                             // full weighting: the fine lane of a coarse point
     int up3[4], up7[6];                           // prolongation: coarse lanes around a fine point
     bool col15, last15, ok7, ok3, odd7;
 
-    __device__ __forceinline__ void init(clds<T> sten, clds<T> wt, clds<T> ch, int n1, int n2)
+    __device__ __forceinline__ void init(clds<T> sten, clds<T> wt, clds<T> ch, lds<T> scratch, int n1, int n2)
     {
         lane = threadIdx.x & 63;
 #pragma unroll
@@ -3046,6 +3047,7 @@ template <typename T, int NC> struct WR {
         w7 = wt[1];
         w3 = wt[2];
         chol = ch;
+        tmp = scratch;
         nu1 = n1;
         nu2 = n2;
         const int b = lane >> 4, c = lane & 15;
@@ -3119,6 +3121,9 @@ template <typename T, int NC> struct WR {
     // substitution in index order, each sum in that order
     __device__ __forceinline__ T solve9(T f) const
     {
+        unsigned at = (unsigned)(uintptr_t)chol;
+        asm volatile("" : "+v"(at));          // read where it is used: kept over the cycle's loops it would spill
+        const clds<T> Lc = (clds<T>)(uintptr_t)at;
         T v[9];
 #pragma unroll
         for (int p = 0; p < 9; ++p) v[p] = lane_of(f, p / 3 * 4 + p % 3);
@@ -3127,45 +3132,49 @@ template <typename T, int NC> struct WR {
         for (int p = 0; p < 9; ++p) {
             T acc = v[p];
 #pragma unroll
-            for (int q = 0; q < p; ++q) acc -= chol[9 * p + q] * v[q];
+            for (int q = 0; q < p; ++q) acc -= Lc[9 * p + q] * v[q];
             ok = ok && div_ok(acc);
-            v[p] = div_fast(acc, chol[9 * p + p], chol[81 + p]);
+            v[p] = div_fast(acc, Lc[9 * p + p], Lc[81 + p]);
         }
 #pragma unroll
         for (int p = 8; p >= 0; --p) {
             T acc = v[p];
 #pragma unroll
-            for (int q = p + 1; q < 9; ++q) acc -= chol[9 * q + p] * v[q];
+            for (int q = p + 1; q < 9; ++q) acc -= Lc[9 * q + p] * v[q];
             ok = ok && div_ok(acc);
-            v[p] = div_fast(acc, chol[9 * p + p], chol[81 + p]);
+            v[p] = div_fast(acc, Lc[9 * p + p], Lc[81 + p]);
         }
-        if (!ok) {   // a dividend outside the range above (zero included): the same with divisions
-#pragma unroll
-            for (int p = 0; p < 9; ++p) v[p] = lane_of(f, p / 3 * 4 + p % 3);
-            solve9_div(v, chol);
-        }
+        if (!ok) return solve9_div(f);
         T x = v[0];
         const int own = (lane >> 2) * 3 + (lane & 3);
 #pragma unroll
         for (int p = 1; p < 9; ++p) x = own == p ? v[p] : x;
         return ok3 ? x : T(0);
     }
-    static __device__ __noinline__ void solve9_div(T (&v)[9], clds<T> L)
+    // a dividend outside the range of div_fast (zero included): the same with divisions, one lane in LDS
+    __device__ __forceinline__ T solve9_div(T f) const
     {
-#pragma unroll
-        for (int p = 0; p < 9; ++p) {
-            T acc = v[p];
-#pragma unroll
-            for (int q = 0; q < p; ++q) acc -= L[9 * p + q] * v[q];
-            v[p] = acc / L[9 * p + p];
+        const int own = (lane >> 2) * 3 + (lane & 3);
+        if (ok3) tmp[own] = f;
+        wave_sync();
+        if (lane == 0) {
+#pragma unroll 1
+            for (int p = 0; p < 9; ++p) {
+                T acc = tmp[p];
+#pragma unroll 1
+                for (int q = 0; q < p; ++q) acc -= chol[9 * p + q] * tmp[q];
+                tmp[p] = acc / chol[9 * p + p];
+            }
+#pragma unroll 1
+            for (int p = 8; p >= 0; --p) {
+                T acc = tmp[p];
+#pragma unroll 1
+                for (int q = p + 1; q < 9; ++q) acc -= chol[9 * q + p] * tmp[q];
+                tmp[p] = acc / chol[9 * p + p];
+            }
         }
-#pragma unroll
-        for (int p = 8; p >= 0; --p) {
-            T acc = v[p];
-#pragma unroll
-            for (int q = p + 1; q < 9; ++q) acc -= L[9 * q + p] * v[q];
-            v[p] = acc / L[9 * p + p];
-        }
+        wave_sync();
+        return ok3 ? tmp[own] : T(0);
     }
 
     __device__ __forceinline__ T sten7x(const T (&s)[9], T v) const
@@ -3289,7 +3298,7 @@ template <typename T, int N, int W> struct RegsLds {
     T ex31[2][2][NB31 + 2][32];
     T f31[N == 63 ? 32 : 1][32], v31[N == 63 ? 33 : 1][33];   // right-hand side of level 31; its solution with a zero ring
     T f15[16][16], v15[17][17];
-    T s[6][9], w[6], chol[90];
+    T s[6][9], w[6], chol[90], tmp[9];
     double red[2 * W];
     int stop;
 };
@@ -3483,7 +3492,8 @@ __global__ void __launch_bounds__(64 * W) k_subtree_regs(SubArgs a)
     if constexpr (N >= 31) l31.init(L.ex31, to_lds<T>((const T*)&L.s[r31][0]), L.w[r31]);
     const bool w0 = tid < 64;
     auto init15 = [&] {
-        wr.init(to_lds<T>((const T*)&L.s[r15][0]), to_lds<T>((const T*)&L.w[r15]), to_lds<T>((const T*)&L.chol[0]), a.nu1, a.nu2);
+        wr.init(to_lds<T>((const T*)&L.s[r15][0]), to_lds<T>((const T*)&L.w[r15]), to_lds<T>((const T*)&L.chol[0]), to_lds<T>(&L.tmp[0]), a.nu1,
+                a.nu2);
     };
     if (N != 63 && w0) init15();
 
@@ -4036,10 +4046,11 @@ hipError_t launch_grid(GridKernel k, bool f32, const StageArgs& a, int32_t nb, h
 template <typename T, int NC>
 static hipError_t launch_regs(const SubArgs& a, hipStream_t s)
 {
+    constexpr int W31 = regs_waves(31, sizeof(T) == 8, NC), W63 = regs_waves(63, sizeof(T) == 8, NC);
     switch (a.regs) {
     case 15: k_subtree_regs<T, 15, 1, NC><<<a.count, 64, 0, s>>>(a); break;
-    case 31: k_subtree_regs<T, 31, REGS_W31, NC><<<a.count, 64 * REGS_W31, 0, s>>>(a); break;
-    case 63: k_subtree_regs<T, 63, REGS_W63, NC><<<a.count, 64 * REGS_W63, 0, s>>>(a); break;
+    case 31: k_subtree_regs<T, 31, W31, NC><<<a.count, 64 * W31, 0, s>>>(a); break;
+    case 63: k_subtree_regs<T, 63, W63, NC><<<a.count, 64 * W63, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -806,13 +806,29 @@ kc_status build_tables(kc_hier* h, const std::vector<char>* active)
     return KC_OK;
 }
 
+// The register kernel runs a call on 63 x 63 in less time than the two grid launches around a call on
+// 31 x 31 take (per cycle, FP64 1023^2, kappa = 1, 2, 3: 65.9, 162, 282 us against 67.2, 170, 305; 16
+// problems in FP32, kappa = 3: 836 against 895 us), so a hierarchy planned on the GPU with the default
+// cutover of 31 takes 63 where that kernel runs its coarse levels and every instance can have a CU
+int effective_cutover(const kc_hier* h)
+{
+    const kc_exec& e = h->ex;
+    if (!h->ws || h->semi || e.mode != 0 || e.coarse_cutover != 31 || e.coarse_threads < 512 || !e.wave_regs ||
+        e.coarse_wave_n != 15 || h->count > 256)
+        return e.coarse_cutover;
+    const int nc = h->hi[0].p.n_coarsest;
+    for (const HostInst& hi : h->hi)
+        if (hi.p.n_coarsest != nc || nc > 3) return e.coarse_cutover;
+    return 63;
+}
+
 // ---------------------------------------------------------------------------
 // execution plan (depends on the exec options): cut depths, op lists, LDS
 // ---------------------------------------------------------------------------
 kc_status plan_exec(kc_hier* h)
 {
     const size_t T = (h->prec == KC_F64) ? 8 : 4;
-    const int cutover = h->ex.coarse_cutover;
+    const int cutover = effective_cutover(h);
     h->max_cut = 0;
     h->max_L = 0;
     h->sub_lds = 0;
@@ -1374,7 +1390,7 @@ std::string launch_name(const kc_hier* h, const Launch& L)
     const char* T = L.f32 ? "float" : "double";
     if (L.type == L_SUB && L.ba.regs)
         return std::string("k_subtree_regs<") + T + ", " + std::to_string(L.ba.regs) + ", " +
-               std::to_string(L.ba.regs == 63 ? REGS_W63 : L.ba.regs == 31 ? REGS_W31 : 1) + ", " + std::to_string(L.ba.coarsest) + ">";
+               std::to_string(regs_waves(L.ba.regs, !L.f32, L.ba.coarsest)) + ", " + std::to_string(L.ba.coarsest) + ">";
     if (L.type == L_SUB)
         return std::string("k_subtree<") + T + ", " + std::to_string(L.threads) + (L.ba.smoother == 1 ? ", true>" : ", false>");
     if (L.type == L_COARSEST) return std::string("k_coarsest<") + T + ">";
