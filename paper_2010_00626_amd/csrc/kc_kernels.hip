@@ -198,7 +198,7 @@ template <int CTRL> __device__ __forceinline__ double dpp(double x)
 constexpr int DPP_WAVE_SHR1 = 0x138;   // wave_shr:1 -> value of lane - 1 (0 in lane 0)
 constexpr int DPP_WAVE_SHL1 = 0x130;   // wave_shl:1 -> value of lane + 1 (0 in lane 63)
 struct Tile {
-    int inst, blk, x0, y0;
+    int x0, y0;
 };
 
 __device__ inline int find_inst(const int32_t* off, int count, int b)
@@ -240,11 +240,11 @@ __device__ __forceinline__ bool finished(int done)
 
 // tile of a level of n points a side (n + 1 a power of two, so the tiles of a row are too)
 template <int BX = TX, int BY = TY>
-__device__ __forceinline__ Tile tile_at(int inst, int blk, int n)
+__device__ __forceinline__ Tile tile_at(int blk, int n)
 {
     static_assert((BX & (BX - 1)) == 0, "tile width");
     const int lgx = max(31 - __clz(n + 1) - __builtin_ctz(BX), 0);
-    return Tile{inst, blk, (blk & ((1 << lgx) - 1)) * BX, (blk >> lgx) * BY};
+    return Tile{(blk & ((1 << lgx) - 1)) * BX, (blk >> lgx) * BY};
 }
 
 // Norms and dot products are Dot2 sums (Ogita, Rump and Oishi, "Accurate sum
@@ -285,10 +285,39 @@ struct Acc2 {
     __device__ __forceinline__ double value() const { return s + c; }
 };
 
+// value of lane ^ OFF, by vector instructions (a lane permute through LDS takes about 130 cycles)
+template <int OFF> __device__ __forceinline__ int lane_xor(int x)
+{
+    if constexpr (OFF == 32 || OFF == 16) {
+        // swaps the upper half (32) or the odd rows of 16 (16) of one operand with the other's lower half or even rows
+        const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                                 : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (threadIdx.x & OFF) ? r[0] : r[1];
+    } else if constexpr (OFF == 8) {
+        return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true);                // row_ror:8
+    } else if constexpr (OFF == 4) {
+        const int up = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xF, 0x5, true);        // row_shl:4 into the even quads
+        return __builtin_amdgcn_update_dpp(up, x, 0x114, 0xF, 0xA, true);               // row_shr:4 into the odd ones
+    } else {
+        return __builtin_amdgcn_update_dpp(0, x, OFF == 2 ? 0x4E : 0xB1, 0xF, 0xF, true);   // quad_perm
+    }
+}
+template <int OFF> __device__ __forceinline__ double lane_xor(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = lane_xor<OFF>((int)(b & 0xffffffffll)), hi = lane_xor<OFF>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// every lane gets the wave's total
 __device__ __forceinline__ void wave_merge(Acc2& v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v.merge(__shfl_xor(v.s, off, 64), __shfl_xor(v.c, off, 64));
+    v.merge(lane_xor<32>(v.s), lane_xor<32>(v.c));
+    v.merge(lane_xor<16>(v.s), lane_xor<16>(v.c));
+    v.merge(lane_xor<8>(v.s), lane_xor<8>(v.c));
+    v.merge(lane_xor<4>(v.s), lane_xor<4>(v.c));
+    v.merge(lane_xor<2>(v.s), lane_xor<2>(v.c));
+    v.merge(lane_xor<1>(v.s), lane_xor<1>(v.c));
 }
 
 // block total of a Dot2 accumulator (valid in thread 0); red holds 2 doubles per wave
@@ -337,11 +366,8 @@ __device__ inline void stop_test(InstState& s, double* hist, int inst, double ss
     else s.iters = k + 1;
 }
 
-__device__ void apply_fin(const StageArgs& a, int inst, double S0, double S1)
+__device__ void apply_fin(const StageArgs& a, int inst, InstState& s, double npts, double S0, double S1)
 {
-    InstState& s = a.st[inst];
-    const InstDev& I = a.inst[inst];
-    const double npts = (double)I.n0 * (double)I.n0;
     switch (a.fin) {
     case FIN_SSF:
         s.ssf = S0;
@@ -420,49 +446,63 @@ __device__ void apply_fin(const StageArgs& a, int inst, double S0, double S1)
     }
 }
 
-// every block of a reducing launch stores its two block sums (value and error
-// term of each); the finalize kernel (one workgroup per instance, launched next
-// on the stream) merges them in block order and applies the solver's decision
-__device__ void reduce_partial(const StageArgs& a, const Tile& t, const Acc2& v0, const Acc2& v1)
+// every block of a reducing launch stores its block sum (value and error term; the gradient's two);
+// the finalize kernel (one workgroup per instance, launched next on the stream) merges them in block
+// order and applies the solver's decision
+__device__ void reduce_partial(const StageArgs& a, const Acc2& v0, const Acc2& v1)
 {
     __shared__ double red[2][2 * (GRID_THREADS / 64)];
+    const bool two = a.fin == FIN_GRAD;
     const Acc2 s0 = block_sum<GRID_THREADS>(v0, red[0]);
-    const Acc2 s1 = block_sum<GRID_THREADS>(v1, red[1]);
+    Acc2 s1;
+    if (two) s1 = block_sum<GRID_THREADS>(v1, red[1]);
     if (threadIdx.x == 0) {
-        const int gb = blockIdx.x;
-        a.partial[4 * gb] = s0.s;
-        a.partial[4 * gb + 1] = s0.c;
-        a.partial[4 * gb + 2] = s1.s;
-        a.partial[4 * gb + 3] = s1.c;
+        double* const p = a.partial + 4 * (size_t)blockIdx.x;
+        p[0] = s0.s;
+        p[1] = s0.c;
+        if (two) {
+            p[2] = s1.s;
+            p[3] = s1.c;
+        }
     }
 }
 
+// merges n partials of one sum: thread t merges partials t, t + 256, ... in that order; loads go in
+// groups of four (clamped indices, masked at use) so that they are in flight together
+__device__ __forceinline__ Acc2 merge_partials(const double* partial, int n, int which)
+{
+    constexpr int G = 4;
+    Acc2 t;
+    const double2* const P2 = (const double2*)partial + which;
+    for (int k0 = threadIdx.x; k0 < n; k0 += G * GRID_THREADS) {
+        double2 p[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) p[g] = P2[2 * (size_t)min(k0 + g * GRID_THREADS, n - 1)];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (k0 + g * GRID_THREADS < n) t.merge(p[g].x, p[g].y);
+    }
+    return t;
+}
+
+// one workgroup on one CU: latency throughout (the state and the first partials are loaded together,
+// the merges of a wave stay in vector registers)
 __global__ void __launch_bounds__(GRID_THREADS) k_finalize(StageArgs a)
 {
     __shared__ double red[2][2 * (GRID_THREADS / 64)];
     const int inst = blockIdx.x;
     const int b0 = a.tile_off[inst], nb = a.tile_off[inst + 1] - b0;
-    if (nb == 0 || a.st[inst].done) return;
-    // thread t merges partials t, t + 256, ... in that order; loads go in groups of
-    // four (clamped indices, masked at use) so that they are in flight together
-    constexpr int G = 4;
-    Acc2 t0, t1;
-    const double4* P4 = (const double4*)a.partial;
-    for (int k0 = threadIdx.x; k0 < nb; k0 += G * GRID_THREADS) {
-        double4 p[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) p[g] = P4[b0 + min(k0 + g * GRID_THREADS, nb - 1)];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (k0 + g * GRID_THREADS < nb) {
-                t0.merge(p[g].x, p[g].y);
-                t1.merge(p[g].z, p[g].w);
-            }
-        }
+    InstState s = a.st[inst];
+    const double n0 = (double)a.inst[inst].n0;
+    if (nb == 0 || s.done) return;
+    const double* const part = a.partial + 4 * (size_t)b0;
+    const Acc2 S0 = block_sum<GRID_THREADS>(merge_partials(part, nb, 0), red[0]);
+    Acc2 S1;
+    if (a.fin == FIN_GRAD) S1 = block_sum<GRID_THREADS>(merge_partials(part, nb, 1), red[1]);
+    if (threadIdx.x == 0) {
+        apply_fin(a, inst, s, n0 * n0, S0.value(), S1.value());
+        a.st[inst] = s;
     }
-    const Acc2 S0 = block_sum<GRID_THREADS>(t0, red[0]);
-    const Acc2 S1 = block_sum<GRID_THREADS>(t1, red[1]);
-    if (threadIdx.x == 0) apply_fin(a, inst, S0.value(), S1.value());
 }
 
 template <typename T> __device__ inline T* buf(const LevelDev& L, int sel) { return (T*)(sel ? L.B : L.A); }
@@ -479,7 +519,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const int n = Lv.n;
-    const Tile t = tile_at(inst, blk, n);
+    const Tile t = tile_at(blk, n);
     const int done = a.st[inst].done;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     Sten<T> s;
@@ -576,7 +616,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
             break;
         }
     }
-    if (kind == GK_NORM) reduce_partial(a, t, nrm, Acc2());
+    if (kind == GK_NORM) reduce_partial(a, nrm, Acc2());
 }
 
 // ---------------------------------------------------------------------------
@@ -1291,7 +1331,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const int n = Lv.n;
-    const Tile t = tile_at<TX, TY>(inst, blk, n);
+    const Tile t = tile_at<TX, TY>(blk, n);
     const int done = a.st[inst].done;
     const gp<const T> A = glob<T>((const void*)Lv.A);
     const gp<T> B = glob<T>(Lv.B);
@@ -1396,7 +1436,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
             Fc[(size_t)Jc * ldc + Ic] = fw_sum(&rs[q], RW);
         }
     }
-    if (a.fin == FIN_STOP) reduce_partial(a, t, nrm, Acc2());
+    if (a.fin == FIN_STOP) reduce_partial(a, nrm, Acc2());
 }
 
 // ---------------------------------------------------------------------------
@@ -1417,7 +1457,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_post(StageArgs a)
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const LevelDev& Lc = I.lev[d + 1];
-    const Tile t = tile_at<TX, TY>(inst, blk, Lv.n);
+    const Tile t = tile_at<TX, TY>(blk, Lv.n);
     const int done = a.st[inst].done;
     const int n = Lv.n, nc = Lc.n, ldc = Lc.lda;
     const gp<T> A = glob<T>(Lv.A);
@@ -1529,7 +1569,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_postpre(StageArgs a)
     const int d = a.depth;
     const LevelDev& Lv = I.lev[d];
     const LevelDev& Lc = I.lev[d + 1];
-    const Tile t = tile_at<TX, TY>(inst, blk, Lv.n);
+    const Tile t = tile_at<TX, TY>(blk, Lv.n);
     const int done = a.st[inst].done;
     const int n = Lv.n, nc = Lc.n;
     const gp<T> B = glob<T>(Lv.B);
@@ -1709,7 +1749,7 @@ __device__ __forceinline__ T fw3(const Row3<T>& S, const Row3<T>& C, const Row3<
 }
 
 struct Strip {
-    int inst, blk, x0, y0;
+    int inst, x0, y0;
     bool live;   // the strip has columns inside the level
 };
 
@@ -1718,7 +1758,6 @@ __device__ inline bool get_strip(const StageArgs& a, Strip& t)
 {
     int blk, nb;
     if (!block_of(a, t.inst, blk, nb)) return false;
-    t.blk = blk;   // the block's partial-sum slot
     const int n = a.inst[t.inst].lev[a.depth].n;
     const int nbx = (n + STRIP_BLOCK_W - 1) / STRIP_BLOCK_W;
     // workgroups go round-robin over the eight XCDs: give each XCD a contiguous run of
@@ -1901,12 +1940,7 @@ __global__ void __launch_bounds__(256) k_pre_s(StageArgs a)
             }
         }
     }
-    if (stop) {
-        Tile tt;
-        tt.inst = t.inst;
-        tt.blk = t.blk;
-        reduce_partial(a, tt, nrm, Acc2());
-    }
+    if (stop) reduce_partial(a, nrm, Acc2());
 }
 
 // post-smoothing: prolong-add + NU sweeps.  Step s reads row i = y0 - H + s,
@@ -3652,7 +3686,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_driver(StageArgs a)
     const InstDev& I = a.inst[inst];
     InstState& st = a.st[inst];
     const int n = I.n0;
-    const Tile t = tile_at(inst, blk, n);
+    const Tile t = tile_at(blk, n);
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int i = t.x0 + tx, jb = t.y0 + ty * DR;
     const int ic = clampi(i, n);
@@ -3829,7 +3863,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_driver(StageArgs a)
             }
         }
     }
-    if (a.fin != FIN_NONE) reduce_partial(a, t, acc0, acc1);
+    if (a.fin != FIN_NONE) reduce_partial(a, acc0, acc1);
 }
 
 // ---------------------------------------------------------------------------
