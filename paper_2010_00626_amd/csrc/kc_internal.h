@@ -8,8 +8,10 @@
 namespace kc {
 
 constexpr int MAXL = 16;          // levels per instance
-constexpr int NTABLES = 1 + 4 * MAXL;   // block tables: whole fine level, fused grid per depth, per level, zebra per level,
-                                        // fused post-smoothing per depth (where its strips differ from the pre-smoothing's)
+constexpr int NTABLES = 2 + 4 * MAXL;   // block tables: whole fine level, fused grid per depth, per level, zebra per level,
+                                        // fused post-smoothing per depth (where its strips differ from the pre-smoothing's),
+                                        // whole fine level in blocks of TRUE_TILES tiles
+constexpr int TRUE_TILES = 4;     // tiles per block of the PCG true-residual kernel
 constexpr int ZLDS_TABLE = 480;   // persistent-kernel LDS elements for the zebra tables of levels 1 .. 63 (4 n each)
 constexpr int TX = 64;            // grid-kernel tile width  (one wave64 row)
 constexpr int TY = 32;            // grid-kernel tile height
@@ -80,8 +82,8 @@ struct InstDev {
     int32_t ldu, ldf;
     double* r;           // PCG residual
     double* z;           // PCG preconditioned residual
-    double* p;           // PCG search direction
-    double* q;           // PCG A p
+    double* p;           // PCG search direction, in p and q by turns (iteration k writes q where k is even)
+    double* q;
     int32_t ldv;         // leading dimension of r, z, p, q
     int32_t n0;          // fine size
     double h2;           // fine h^2
@@ -219,10 +221,9 @@ enum GridKernel : int32_t {
     GK_IR_UPDATE = 13, // u += A32 / scale
     GK_PCG_INIT = 14,  // u = 0, r = F, ||r||^2
     GK_PCG_PRECIN = 15,// level-0 cycle input from r (FP32 scaled copy or FP64 alias)
-    GK_PCG_RZ = 16,    // z from the cycle (FP32 -> FP64 unscale), r.z, beta
-    GK_PCG_P = 21,     // p = z + beta p
-    GK_PCG_AP = 17,    // q = S p, p.q, alpha
-    GK_PCG_UPD = 18,   // u += alpha p, r -= alpha q, ||r||^2
+    GK_PCG_RZ = 16,    // r.z, beta (z: the cycle's result, FP32 -> FP64 unscaled)
+    GK_PCG_AP = 17,    // p = z + beta p, q = S p, p.q, alpha
+    GK_PCG_UPD = 18,   // q = S p, u += alpha p, r -= alpha q, ||r||^2
     GK_APPLY = 19,     // y = S x / h^2
     GK_GRAD = 20,      // -lam^T dS u / h^2 for theta and eps
     GK_ZERO_SELF = 22, // unfused: A[d] = 0 on the launch's own level

@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_finalize(StageArgs a)
     const int b0 = a.tile_off[inst], nb = a.tile_off[inst + 1] - b0;
     InstState s = a.st[inst];
     const double n0 = (double)a.inst[inst].n0;
-    if (nb == 0 || s.done) return;
+    if (nb == 0 || s.done || (a.fin == FIN_PCG_TRUE && !s.check)) return;
     const double* const part = a.partial + 4 * (size_t)b0;
     const Acc2 S0 = block_sum<GRID_THREADS>(merge_partials(part, nb, 0), red[0]);
     Acc2 S1;
@@ -3678,6 +3678,46 @@ struct DWin {
     }
 };
 
+// the same rows of a column, its neighbours by lane shifts; the wave's first and last lanes load the
+// column beside it (the other lanes their own once more)
+struct DCol {
+    double c[DR + 2], e[DR + 2];
+    static __device__ __forceinline__ int edge(int i, int lane) { return lane == 0 ? i - 1 : lane == 63 ? i + 1 : i; }
+    template <typename T>
+    __device__ __forceinline__ void load(gp<const T> x, int ld, int n, int jb, int i, int lane)
+    {
+        const int ic = clampi(i, n), ie = clampi(edge(i, lane), n);
+#pragma unroll
+        for (int r = 0; r < DR + 2; ++r) {
+            const size_t o = (size_t)clampi(jb - 1 + r, n) * ld;
+            c[r] = (double)x[o + ic];
+            e[r] = (double)x[o + ie];
+        }
+    }
+    __device__ __forceinline__ void mask(int n, int jb, int i, int lane)
+    {
+        const int ie = edge(i, lane);
+#pragma unroll
+        for (int r = 0; r < DR + 2; ++r) {
+            c[r] = inside(jb - 1 + r, i, n) ? c[r] : 0.0;
+            e[r] = inside(jb - 1 + r, ie, n) ? e[r] : 0.0;
+        }
+    }
+    // stencil sum at grid row jb + r
+    __device__ __forceinline__ double apply(const Sten<double>& s, int r, int lane) const
+    {
+        double acc = 0.0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const double w = dpp<DPP_WAVE_SHR1>(c[r + b]), x = dpp<DPP_WAVE_SHL1>(c[r + b]);
+            acc = fmadd(s.c[3 * b], lane == 0 ? e[r + b] : w, acc);
+            acc = fmadd(s.c[3 * b + 1], c[r + b], acc);
+            acc = fmadd(s.c[3 * b + 2], lane == 63 ? e[r + b] : x, acc);
+        }
+        return acc;
+    }
+};
+
 template <bool F32, int kind>
 __global__ void __launch_bounds__(GRID_THREADS) k_driver(StageArgs a)
 {
@@ -3695,10 +3735,12 @@ __global__ void __launch_bounds__(GRID_THREADS) k_driver(StageArgs a)
     const double h2 = I.h2;
     Acc2 acc0, acc1;
     const LevelDev& L0 = I.lev[0];
-    const double scale = st.scale, scale_used = st.scale_used;
+    const double scale = st.scale;
+    // quotients by the scale, a power of two, are products by its inverse
+    const double unscale = 1.0 / (kind == GK_IR_UPDATE ? st.scale_used : st.scale);
     const double alpha = st.alpha, beta = st.beta;
     const bool first = st.iters == 0;
-    const gp<double> U = glob<double>(I.u), R = glob<double>(I.r), Z = glob<double>(I.z), Pv = glob<double>(I.p),
+    const gp<double> U = glob<double>(I.u), R = glob<double>(I.r), Pv = glob<double>(I.p),
                      Q = glob<double>(I.q), Y = glob<double>(I.y);
     const gp<const double> Fv = glob<double>((const void*)I.f), X = glob<double>((const void*)I.x);
     const gp<const double> Yc = glob<double>((const void*)I.y), Pc = glob<double>((const void*)I.p),
@@ -3746,7 +3788,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_driver(StageArgs a)
         }
 #pragma unroll
         for (int r = 0; r < DR; ++r)
-            if (ok(r)) U[rowu(r)] = V[r] + E[r] / scale_used;
+            if (ok(r)) U[rowu(r)] = V[r] + E[r] * unscale;
     } else if constexpr (kind == GK_PCG_INIT) {
         double F[DR];
 #pragma unroll
@@ -3776,64 +3818,74 @@ __global__ void __launch_bounds__(GRID_THREADS) k_driver(StageArgs a)
         }
 #pragma unroll
         for (int r = 0; r < DR; ++r) {
-            const double z = F32 ? E[r] / scale : E[r];
-            if (ok(r)) {
-                if (F32) Z[rowv(r)] = z;
-                acc0.add_prod(V[r], z);
-            }
+            const double z = F32 ? E[r] * unscale : E[r];
+            if (ok(r)) acc0.add_prod(V[r], z);
         }
-    } else if constexpr (kind == GK_PCG_P) {
-        double E[DR], V[DR];
-#pragma unroll
-        for (int r = 0; r < DR; ++r) {
-            E[r] = Zc[rowv(r)];
-            V[r] = first ? 0.0 : Pc[rowv(r)];
-        }
-#pragma unroll
-        for (int r = 0; r < DR; ++r)
-            if (ok(r)) Pv[rowv(r)] = first ? E[r] : E[r] + beta * V[r];
     } else if constexpr (kind == GK_PCG_AP) {
-        DWin<double> w;
-        w.load(Pc, I.ldv, n, jb, i);
+        // p = z + beta p, q = S p and p.q in one pass: q is not kept (the update forms it again from p),
+        // so p alternates between the two arrays, whose other one the neighbouring tiles still read
+        const gp<const double> Po = st.iters & 1 ? Qc : Pc;
+        const gp<double> Pn = st.iters & 1 ? Pv : Q;
+        DCol w, wz;
+        if constexpr (F32) wz.load(A32, L0.lda, n, jb, i, tx);
+        else wz.load(Zc, I.ldv, n, jb, i, tx);
+        w.load(Po, I.ldv, n, jb, i, tx);
+        const double un = F32 ? unscale : 1.0;
+#pragma unroll
+        for (int r = 0; r < DR + 2; ++r) {
+            const double zc = F32 ? wz.c[r] * un : wz.c[r], ze = F32 ? wz.e[r] * un : wz.e[r];
+            w.c[r] = first ? zc : zc + beta * w.c[r];
+            w.e[r] = first ? ze : ze + beta * w.e[r];
+        }
+        w.mask(n, jb, i, tx);
 #pragma unroll
         for (int r = 0; r < DR; ++r) {
-            const double q = w.apply(s, r);
+            const double q = w.apply(s, r, tx);
             if (ok(r)) {
-                Q[rowv(r)] = q;
-                acc0.add_prod(w.v[r + 1][1], q);
+                Pn[rowv(r)] = w.c[r + 1];
+                acc0.add_prod(w.c[r + 1], q);
             }
         }
     } else if constexpr (kind == GK_PCG_UPD) {
-        double V[DR], Pp[DR], Rr[DR], Qq[DR];
+        const gp<const double> Pk = st.iters & 1 ? Pc : Qc;   // this iteration's p
+        DCol w;
+        w.load(Pk, I.ldv, n, jb, i, tx);
+        double V[DR], Rr[DR];
 #pragma unroll
         for (int r = 0; r < DR; ++r) {
             V[r] = Uc[rowu(r)];
-            Pp[r] = Pc[rowv(r)];
             Rr[r] = Rc[rowv(r)];
-            Qq[r] = Qc[rowv(r)];
         }
+        w.mask(n, jb, i, tx);
 #pragma unroll
         for (int r = 0; r < DR; ++r) {
-            const double res = Rr[r] - alpha * Qq[r];
+            const double res = Rr[r] - alpha * w.apply(s, r, tx);
             if (ok(r)) {
-                U[rowu(r)] = V[r] + alpha * Pp[r];
+                U[rowu(r)] = V[r] + alpha * w.c[r + 1];
                 R[rowv(r)] = res;
                 acc0.add_sq(res);
             }
         }
     } else if constexpr (kind == GK_PCG_TRUE) {
         if (!st.check) return;   // uniform over the block: no barrier is skipped by part of it
-        DWin<double> w;
-        w.load(Uc, I.ldu, n, jb, i);
-        double F[DR];
+        // a block takes TRUE_TILES tiles: nearly every launch finds nothing to do, and its blocks cost
+#pragma unroll 1
+        for (int k = 0; k < TRUE_TILES; ++k) {
+            const Tile tk = tile_at(TRUE_TILES * blk + k, n);
+            const int ik = tk.x0 + tx, jk = tk.y0 + ty * DR;
+            if (tk.y0 >= n) break;
+            DWin<double> w;
+            w.load(Uc, I.ldu, n, jk, ik);
+            double F[DR];
 #pragma unroll
-        for (int r = 0; r < DR; ++r) F[r] = Fv[rowf(r)];
+            for (int r = 0; r < DR; ++r) F[r] = Fv[(size_t)clampi(jk + r, n) * I.ldf + clampi(ik, n)];
 #pragma unroll
-        for (int r = 0; r < DR; ++r) {
-            const double res = h2 * F[r] - w.apply(s, r);
-            if (ok(r)) {
-                R[rowv(r)] = res;
-                acc0.add_sq(res);
+            for (int r = 0; r < DR; ++r) {
+                const double res = h2 * F[r] - w.apply(s, r);
+                if (jk + r < n && ik < n) {
+                    R[(size_t)(jk + r) * I.ldv + ik] = res;
+                    acc0.add_sq(res);
+                }
             }
         }
     } else if constexpr (kind == GK_APPLY) {
@@ -4002,7 +4054,6 @@ static hipError_t launch_driver(GridKernel k, const StageArgs& a, int nb, hipStr
     case GK_PCG_INIT: k_driver<F32, GK_PCG_INIT><<<g, b, 0, s>>>(a); break;
     case GK_PCG_PRECIN: k_driver<F32, GK_PCG_PRECIN><<<g, b, 0, s>>>(a); break;
     case GK_PCG_RZ: k_driver<F32, GK_PCG_RZ><<<g, b, 0, s>>>(a); break;
-    case GK_PCG_P: k_driver<F32, GK_PCG_P><<<g, b, 0, s>>>(a); break;
     case GK_PCG_AP: k_driver<F32, GK_PCG_AP><<<g, b, 0, s>>>(a); break;
     case GK_PCG_UPD: k_driver<F32, GK_PCG_UPD><<<g, b, 0, s>>>(a); break;
     case GK_PCG_TRUE: k_driver<F32, GK_PCG_TRUE><<<g, b, 0, s>>>(a); break;

@@ -470,6 +470,7 @@ int tt_cut(int d) { return 1 + d; }          // instances with cut > d
 int tt_lvl(int d) { return 1 + MAXL + d; }   // instances with L - 1 > d and cut > d (one kernel per operation)
 int tt_zeb(int d) { return 1 + 2 * MAXL + d; }   // zebra line groups of those instances
 int tt_cut_post(int d) { return 1 + 3 * MAXL + d; }   // fused post-smoothing strips where they differ from tt_cut
+int tt_true() { return 1 + 4 * MAXL; }       // whole fine level, TRUE_TILES tiles per block
 int lt_sub(int d) { return d; }              // instances with cut == d
 int lt_coarse(int d) { return MAXL + d; }    // instances with L - 1 == d
 
@@ -767,6 +768,7 @@ kc_status build_tables(kc_hier* h, const std::vector<char>* active)
         const HostInst& hi = h->hi[i];
         const int L = hi.il.L;
         h->tiles[tt_all0()][i + 1] = tiles_of(hi.il.n[0]);
+        h->tiles[tt_true()][i + 1] = (tiles_of(hi.il.n[0]) + TRUE_TILES - 1) / TRUE_TILES;
         for (int d = 0; d < MAXL; ++d) {
             const int sh = h->shape[d];
             const int tc = (sh & 2)    ? tiles_stream(hi.il.n[d], (sh >> 2) & 3)
@@ -1111,14 +1113,13 @@ void iteration(kc_hier* h, int drv, const kc_cycle_params& c, std::vector<Launch
         Launch rz = grid(h, GK_PCG_RZ, f32, tt_all0(), 0);
         rz.sa.fin = FIN_RZ;
         out.push_back(rz);
-        out.push_back(grid(h, GK_PCG_P, f32, tt_all0(), 0));
         Launch ap = grid(h, GK_PCG_AP, f32, tt_all0(), 0);
         ap.sa.fin = FIN_PQ;
         out.push_back(ap);
         Launch up = grid(h, GK_PCG_UPD, f32, tt_all0(), 0);
         up.sa.fin = FIN_PCG_R;
         out.push_back(up);
-        Launch tr = grid(h, GK_PCG_TRUE, false, tt_all0(), 0);
+        Launch tr = grid(h, GK_PCG_TRUE, false, tt_true(), 0);
         tr.sa.fin = FIN_PCG_TRUE;
         out.push_back(tr);
         break;
@@ -1479,10 +1480,9 @@ void launch_work(const kc_hier* h, const Launch& L, double& bytes, double& flops
         case GK_SSF: bytes += N * 8.0; break;
         case GK_PCG_INIT: bytes += N * 24.0; break;          // read f; write u, r
         case GK_PCG_PRECIN: bytes += N * (L.f32 ? 12.0 : 0.0); break;
-        case GK_PCG_RZ: bytes += N * (L.f32 ? 20.0 : 24.0); break;
-        case GK_PCG_P: bytes += N * 24.0; break;
-        case GK_PCG_AP: bytes += N * 16.0; break;
-        case GK_PCG_UPD: bytes += N * 48.0; break;
+        case GK_PCG_RZ: bytes += N * (L.f32 ? 12.0 : 16.0); break;    // read z, r
+        case GK_PCG_AP: bytes += N * (L.f32 ? 20.0 : 24.0); break;    // read z, p; write p
+        case GK_PCG_UPD: bytes += N * 40.0; break;                    // read p, u, r; write u, r
         default: break;
         }
     }
