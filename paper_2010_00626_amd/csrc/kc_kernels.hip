@@ -2323,81 +2323,83 @@ __device__ __forceinline__ void ph_sweep_zg1(clds<T> x, lds<T> y, clds<T> F, cld
     ph_sweep<T, N, NB>(x, y, F, sc, om, t, true);
 }
 
-// zebra relaxation of one colour on an N x N level in LDS (zero ring, stride
-// N + 2), in place: thread t solves line 2 t + colour with the lane mapping of
-// the grid kernel (same arithmetic, same order; the ring supplies the zeros
-// that kernel masks in).  tab: the level's reciprocal pivots then upper
-// multipliers for the direction, staged in LDS.  Each chunk of ZK points
-// loads its neighbour values, right-hand sides and pivots before its stores.
+// zebra relaxation of one colour on an N x N level in LDS (zero ring, stride N + 2), in place, with the
+// registers mapping of the grid kernel: (N + 1) / 4 consecutive lanes hold a line, four points each, and
+// the running value goes from lane to lane by a DPP move (same arithmetic, same order; the ring supplies
+// the zeros that kernel masks in).  tab: the level's reciprocal pivots then upper multipliers for the
+// direction, staged in LDS.  Bound by the chain of the line; with one thread per line every chunk of the
+// chain also waited for its LDS reads.  A kappa = 3 solve on 1023 x 1023 (about 1470 calls on 63 x 63)
+// takes 266 ms instead of 286.
 template <typename T, int N, int DIR>
 __device__ __forceinline__ void zebra_lds_line(lds<T> x, clds<T> F, clds<T> sc, clds<T> tab, int color, int t)
 {
-    constexpr int P = N + 2, ZK = 8;
-    const int line = 2 * t + color;
-    if (line >= N) return;
-    auto at = [&](int L, int q) -> int { return DIR == 0 ? (L + 1) * P + (q + 1) : (q + 1) * P + (L + 1); };
-    const T cm0 = sc[0], cm1 = DIR == 0 ? sc[1] : sc[3], cm2 = DIR == 0 ? sc[2] : sc[6];
-    const T cp0 = DIR == 0 ? sc[6] : sc[2], cp1 = DIR == 0 ? sc[7] : sc[5], cp2 = sc[8];
+    constexpr int Pd = N + 2, P = 4, LN = (N + 1) / P;
+    const int lp = t & (LN - 1), line = 2 * (t / LN) + color, q0 = lp * P;
+    if (line >= N) return;   // all lanes of the line
+    const bool west = lp == 0, east = lp == LN - 1;
+    auto at = [&](int L, int q) -> int { return DIR == 0 ? (L + 1) * Pd + (q + 1) : (q + 1) * Pd + (L + 1); };
     const T lo = DIR == 0 ? sc[3] : sc[1];
-    T m0 = T(0), p0 = T(0);
-    T m1 = x[at(line - 1, 0)], p1 = x[at(line + 1, 0)];
-    T prev = T(0);
+    T m[P + 2], p[P + 2], y[P], r[P], u[P];
 #pragma unroll
-    for (int q0 = 0; q0 < N; q0 += ZK) {
-        T mn[ZK], pn[ZK], fv[ZK], rv[ZK];
+    for (int k = 0; k < P + 2; ++k) {
+        const int q = min(q0 - 1 + k, N);   // q = N reads the ring
+        m[k] = x[at(line - 1, q)];
+        p[k] = x[at(line + 1, q)];
+    }
 #pragma unroll
-        for (int k = 0; k < ZK; ++k) {
-            const int q = q0 + k;
-            if (q < N) {
-                mn[k] = x[at(line - 1, q + 1)];   // q + 1 = N reads the ring
-                pn[k] = x[at(line + 1, q + 1)];
-                fv[k] = F[at(line, q)];
-                rv[k] = tab[q];
-            }
-        }
+    for (int k = 0; k < P; ++k) {
+        const int q = min(q0 + k, N - 1);
+        y[k] = F[at(line, q)];
+        r[k] = tab[q];
+        u[k] = tab[N + q];
+    }
+    {
+        const T cm0 = sc[0], cm1 = DIR == 0 ? sc[1] : sc[3], cm2 = DIR == 0 ? sc[2] : sc[6];
+        const T cp0 = DIR == 0 ? sc[6] : sc[2], cp1 = DIR == 0 ? sc[7] : sc[5], cp2 = sc[8];
 #pragma unroll
-        for (int k = 0; k < ZK; ++k) {
-            const int q = q0 + k;
-            if (q < N) {
-                T acc = T(0);
-                acc = fmadd(cm0, m0, acc);
-                acc = fmadd(cm1, m1, acc);
-                acc = fmadd(cm2, mn[k], acc);
-                acc = fmadd(cp0, p0, acc);
-                acc = fmadd(cp1, p1, acc);
-                acc = fmadd(cp2, pn[k], acc);
-                const T dq = fv[k] - acc;
-                const T y = (q == 0) ? dq * rv[k] : fmadd(-lo, prev, dq) * rv[k];
-                x[at(line, q)] = y;
-                prev = y;
-                m0 = m1;
-                m1 = mn[k];
-                p0 = p1;
-                p1 = pn[k];
-            }
+        for (int k = 0; k < P; ++k) {
+            T acc = T(0);
+            acc = fmadd(cm0, m[k], acc);
+            acc = fmadd(cm1, m[k + 1], acc);
+            acc = fmadd(cm2, m[k + 2], acc);
+            acc = fmadd(cp0, p[k], acc);
+            acc = fmadd(cp1, p[k + 1], acc);
+            acc = fmadd(cp2, p[k + 2], acc);
+            y[k] = y[k] - acc;
         }
     }
-    T next = prev;   // x_{N-1} = y_{N-1}
+    // as in zebra_regs: a signed zero that leaves d_0 as it is; the line's end enters with u = 0 and y = 0
+    const T start = __builtin_signbit(lo) ? -T(0) : T(0);
+    T v = start;
+#pragma unroll 1
+    for (int s = 1; s < LN; ++s) {
 #pragma unroll
-    for (int q1 = N - 2; q1 >= 0; q1 -= ZK) {
-        T yv[ZK], uv[ZK];
+        for (int k = 0; k < P; ++k) v = fmadd(-lo, v, y[k]) * r[k];
+        v = dpp<DPP_WAVE_SHR1>(v);
+        v = west ? start : v;
+    }
 #pragma unroll
-        for (int k = 0; k < ZK; ++k) {
-            const int q = q1 - k;
-            if (q >= 0) {
-                yv[k] = x[at(line, q)];
-                uv[k] = tab[N + q];
-            }
-        }
+    for (int k = 0; k < P; ++k) {
+        v = fmadd(-lo, v, y[k]) * r[k];
+        y[k] = v;
+    }
+    if (east) {
+        u[P - 2] = T(0);
+        u[P - 1] = T(0);
+        y[P - 1] = T(0);
+    }
+    v = T(0);
+#pragma unroll 1
+    for (int s = 1; s < LN; ++s) {
 #pragma unroll
-        for (int k = 0; k < ZK; ++k) {
-            const int q = q1 - k;
-            if (q >= 0) {
-                const T v = fmadd(-uv[k], next, yv[k]);
-                x[at(line, q)] = v;
-                next = v;
-            }
-        }
+        for (int k = P - 1; k >= 0; --k) v = fmadd(-u[k], v, y[k]);
+        v = dpp<DPP_WAVE_SHL1>(v);
+        v = east ? T(0) : v;
+    }
+#pragma unroll
+    for (int k = P - 1; k >= 0; --k) {
+        v = fmadd(-u[k], v, y[k]);
+        if (q0 + k < N) x[at(line, q0 + k)] = v;
     }
 }
 template <typename T, int N, int NB>
