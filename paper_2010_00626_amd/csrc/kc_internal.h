@@ -19,6 +19,7 @@ constexpr int TS = 16;            // small-level tile side of the fused kernels
 constexpr int TM = 32;            // mid-level tile side of the fused kernels
 constexpr int TT = 8;             // tiny tile side of the fused kernels (one point per thread and phase)
 constexpr int STRIP_BLOCK_W = 216; // columns of a streaming block (4 strips of 54)
+constexpr int FLAG_IN_PLACE = 64; // fused kernels without sweeps: estimate in place on A, coarse estimate set to zero
 constexpr int GRID_THREADS = 256; // threads of the grid-wide kernels
 constexpr int ZREG_N = 63;        // zebra line kernel: shortest line of the registers mapping
 // points per lane of that mapping, from the longest line of a launch
@@ -230,6 +231,8 @@ enum GridKernel : int32_t {
     GK_POSTPRE = 23,   // fused junction of sibling calls: post (nu2 = src) of the first + pre (nu) of the second
     GK_ZEBRA = 24,     // zebra line relaxation in place on buffer src, lines of colour dst, direction nu (0 x, 1 y); zg and
                        // flags: zebra_args
+    GK_SEMI_DOWN = 26, // semi-coarsened: residual of A, F[d+1] = R r, A[d+1] = 0
+    GK_SEMI_UP = 27,   // semi-coarsened: dst += P A[d+1]
     GK_PCG_TRUE = 25,  // instances with check set: r = F - S u (FP64, replaces the recurrence residual), ||r||^2
 };
 

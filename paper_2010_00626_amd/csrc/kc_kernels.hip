@@ -622,13 +622,18 @@ __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
 // ---------------------------------------------------------------------------
 // semi-coarsened levels (Section 4, fifth and sixth solvers): level d has n
 // lines (rows) of nx points, x is never coarsened, and every stencil is in units
-// of the fine level's h^2 (F of every level carries the same h^2 scale).  One
-// kernel per operation on 64 x 32 tiles of (nx, n):
+// of the fine level's h^2 (F of every level carries the same h^2 scale).
+// Relaxation is the x-line zebra kernel; the operations between it and the
+// coarse calls run as one launch each way on 64 x 32 tiles of (nx, n):
 //   residual      r = F - S v (the nine products south row first, west to east);
 //   restriction   F_c(J, i) = 1/4 r(2J, i) + 1/2 r(2J+1, i) + 1/4 r(2J+2, i), i.e. R = P^T / 2;
 //   prolongation  e(2J+1, i) = v_c(J, i), e(2J, i) = 1/2 v_c(J-1, i) + 1/2 v_c(J, i)
 //                 (linear interpolation along y, zero beyond the last lines);
-//   zero, add, copy as in the square case.  Relaxation is the x-line zebra kernel.
+//   zero and add as in the square case.
+// Every load of a thread's lines is issued before the first use; the residual
+// stays in registers.  One kernel per operation (residual, restriction, zero;
+// prolongation, add) took 5 launches of 5 to 22 us per visit of a level, most
+// of it waiting for loads: a kappa = F cycle on 1023 x 1023 took 7.2 ms, now 6.6.
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ inline T sload(const T* p, int ld, int ny, int nx, int j, int i)
@@ -652,53 +657,57 @@ __global__ void __launch_bounds__(GRID_THREADS) k_semi(StageArgs a)
     const int x0 = (blk % tiles_x) * TX, y0 = (blk / tiles_x) * TY;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int i = x0 + tx;
-    const int lds_ = a.src ? Lv.ldb : Lv.lda;
-    const int ldd_ = a.dst ? Lv.ldb : Lv.lda;
 
-    if constexpr (kind == GK_RESTRICT || kind == GK_ZERO) {
-        // coarse lines J whose centre line 2J+1 lies in this tile
+    if constexpr (kind == GK_SEMI_DOWN) {
+        // residual, full weighting and the coarse level's zero guess: a thread forms the residual of
+        // the lines 2J, 2J + 1 and 2J + 2 of its column (the last one again for the next coarse line)
         const LevelDev& Lc = I.lev[d + 1];
         const int nyc = Lc.n;
-        const T* r = buf<T>(Lv, a.src);
-        for (int k = ty; k < TY / 2; k += GRID_THREADS / 64) {
-            const int J = (y0 >> 1) + k;
-            if (J >= nyc || i >= nx) continue;
-            if constexpr (kind == GK_ZERO) {
-                ((T*)Lc.A)[(size_t)J * Lc.lda + i] = T(0);
-            } else {
+        const T* x = (const T*)Lv.A;
+        const T* f = (const T*)Lv.F;
+        Sten<T> s;
+        s.load(Prec<T>::s(I, d));
+        const T fs = (T)Lv.fscale;
+        constexpr int U = (TY / 2) / (GRID_THREADS / 64);   // coarse lines of a thread, one below the other
+        const int J0 = (y0 >> 1) + ty * U, ic = min(i, nx - 1), j0 = 2 * J0;
+        T w[2 * U + 3][3], fv[2 * U + 1];
+#pragma unroll
+        for (int k = 0; k < 2 * U + 3; ++k)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) w[k][e] = sload(x, Lv.lda, ny, nx, j0 - 1 + k, i - 1 + e);
+#pragma unroll
+        for (int k = 0; k < 2 * U + 1; ++k) fv[k] = f[(size_t)min(j0 + k, ny - 1) * Lv.ldf + ic];
+        T r[2 * U + 1];
+#pragma unroll
+        for (int k = 0; k < 2 * U + 1; ++k) {
+            T acc = T(0);
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+#pragma unroll
+                for (int e = 0; e < 3; ++e) acc = fmadd(s.c[3 * b + e], w[k + b][e], acc);
+            r[k] = fs * fv[k] - acc;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int J = J0 + k;
+            if (J < nyc && i < nx) {
                 T acc = T(0);
-                acc += T(0.25) * r[(size_t)(2 * J) * lds_ + i];
-                acc += T(0.5) * r[(size_t)(2 * J + 1) * lds_ + i];
-                acc += T(0.25) * r[(size_t)(2 * J + 2) * lds_ + i];
+                acc += T(0.25) * r[2 * k];
+                acc += T(0.5) * r[2 * k + 1];
+                acc += T(0.25) * r[2 * k + 2];
                 ((T*)Lc.F)[(size_t)J * Lc.ldf + i] = acc;
+                ((T*)Lc.A)[(size_t)J * Lc.lda + i] = T(0);
             }
         }
         return;
     }
-    Sten<T> s;
-    s.load(Prec<T>::s(I, d));
-    const T fs = (T)Lv.fscale;
     for (int k = ty; k < TY; k += GRID_THREADS / 64) {
         const int j = y0 + k;
         if (j >= ny || i >= nx) continue;
-        const size_t gs = (size_t)j * lds_ + i, gd = (size_t)j * ldd_ + i;
-        if constexpr (kind == GK_RESID) {
-            const T* x = buf<T>(Lv, a.src);
-            T acc = T(0);
-            acc = fmadd(s.c[0], sload(x, lds_, ny, nx, j - 1, i - 1), acc);
-            acc = fmadd(s.c[1], sload(x, lds_, ny, nx, j - 1, i), acc);
-            acc = fmadd(s.c[2], sload(x, lds_, ny, nx, j - 1, i + 1), acc);
-            acc = fmadd(s.c[3], sload(x, lds_, ny, nx, j, i - 1), acc);
-            acc = fmadd(s.c[4], sload(x, lds_, ny, nx, j, i), acc);
-            acc = fmadd(s.c[5], sload(x, lds_, ny, nx, j, i + 1), acc);
-            acc = fmadd(s.c[6], sload(x, lds_, ny, nx, j + 1, i - 1), acc);
-            acc = fmadd(s.c[7], sload(x, lds_, ny, nx, j + 1, i), acc);
-            acc = fmadd(s.c[8], sload(x, lds_, ny, nx, j + 1, i + 1), acc);
-            buf<T>(Lv, a.dst)[gd] = fs * ((const T*)Lv.F)[(size_t)j * Lv.ldf + i] - acc;
-        } else if constexpr (kind == GK_PROLONG) {
+        if constexpr (kind == GK_SEMI_UP) {
             const LevelDev& Lc = I.lev[d + 1];
-            const T* vc = buf<T>(Lc, a.src);
-            const int ldc = a.src ? Lc.ldb : Lc.lda, nyc = Lc.n;
+            const T* vc = (const T*)Lc.A;
+            const int ldc = Lc.lda, nyc = Lc.n;
             T acc = T(0);
             if (j & 1) {
                 acc += T(1) * vc[(size_t)(j >> 1) * ldc + i];
@@ -708,12 +717,8 @@ __global__ void __launch_bounds__(GRID_THREADS) k_semi(StageArgs a)
                 acc += T(0.5) * (Ja >= 0 ? va : T(0));
                 acc += T(0.5) * (Jb < nyc ? vb : T(0));
             }
-            buf<T>(Lv, a.dst)[gd] = acc;
-        } else if constexpr (kind == GK_ADD) {
-            T* v = buf<T>(Lv, a.src);
-            v[gs] = v[gs] + buf<T>(Lv, a.dst)[gd];
-        } else if constexpr (kind == GK_COPY) {
-            buf<T>(Lv, a.dst)[gd] = buf<T>(Lv, a.src)[gs];
+            T* v = (T*)Lv.A + (size_t)j * Lv.lda + i;
+            *v = *v + acc;
         } else if constexpr (kind == GK_ZERO_SELF) {
             ((T*)Lv.A)[(size_t)j * Lv.lda + i] = T(0);
         }
@@ -1316,7 +1321,11 @@ __device__ __forceinline__ void band_sweeps(T (*sv)[RW * RH], const T* sf, const
 
 // ---------------------------------------------------------------------------
 // fused pre-smoothing: nu sweeps + residual + full weighting in one pass
-// (input region = tile + halo nu+1, swept in LDS); optional input norm
+// (input region = tile + halo nu+1, swept in LDS); optional input norm.  With
+// FLAG_IN_PLACE (no sweeps; zebra relaxation, which works in place on A) the
+// estimate is not written again and the coarse level's is set to zero: the
+// three kernels of Algorithm 4 between the relaxation and the coarse call in
+// one; the post-smoothing kernel likewise adds the correction to A itself.
 // ---------------------------------------------------------------------------
 template <typename T, int NU, int TX, int TY>
 __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
@@ -1409,7 +1418,8 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     T* rs = sv[(NU + 1) & 1];
 
     // smoothed estimate on the tile
-    for (int p = threadIdx.x; p < TX * TY; p += GRID_THREADS) {
+    const bool in_place = NU == 0 && (a.flags & FLAG_IN_PLACE);
+    for (int p = threadIdx.x; p < (in_place ? 0 : TX * TY); p += GRID_THREADS) {
         const int y = p / TX, x = p % TX;
         const int j = t.y0 + y, i = t.x0 + x;
         if (j < n && i < n) B[(size_t)j * Lv.ldb + i] = vs[(H + y) * RW + (H + x)];
@@ -1434,6 +1444,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
             if (Ic >= nc || Jc >= nc) continue;
             const int q = (2 * Jc + 1 - ry0) * RW + (2 * Ic + 1 - rx0);
             Fc[(size_t)Jc * ldc + Ic] = fw_sum(&rs[q], RW);
+            if (in_place) glob<T>(Lc.A)[(size_t)Jc * Lc.lda + Ic] = T(0);
         }
     }
     if (a.fin == FIN_STOP) reduce_partial(a, nrm, Acc2());
@@ -1460,8 +1471,10 @@ __global__ void __launch_bounds__(GRID_THREADS) k_post(StageArgs a)
     const Tile t = tile_at<TX, TY>(blk, Lv.n);
     const int done = a.st[inst].done;
     const int n = Lv.n, nc = Lc.n, ldc = Lc.lda;
+    const bool in_place = NU == 0 && (a.flags & FLAG_IN_PLACE);
     const gp<T> A = glob<T>(Lv.A);
-    const gp<const T> B = glob<T>((const void*)Lv.B);
+    const gp<const T> B = in_place ? (gp<const T>)A : glob<T>((const void*)Lv.B);
+    const size_t ldb = in_place ? Lv.lda : Lv.ldb;
     const gp<const T> F = glob<T>((const void*)Lv.F);
     const gp<const T> Vc = glob<T>((const void*)Lc.A);
     const T fs = (T)Lv.fscale;
@@ -1483,7 +1496,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_post(StageArgs a)
             const bool in = p < NR && inside(j, i, n);
             const size_t jc = (size_t)clampi(j, n), ic = (size_t)clampi(i, n);
             const T lf = F[jc * Lv.ldf + ic];
-            const T lv = B[jc * Lv.ldb + ic];
+            const T lv = B[jc * ldb + ic];
             fa[k] = in ? fs * lf : T(0);
             va[k] = in ? lv : T(0);
         }
@@ -1835,7 +1848,7 @@ __global__ void __launch_bounds__(256) k_pre_s(StageArgs a)
     Sten<T> s;
     s.load(Prec<T>::s(I, d));
     const T w = Prec<T>::w(I, d);
-    const bool zg = a.zg != 0, stop = a.fin == FIN_STOP;
+    const bool zg = a.zg != 0, stop = a.fin == FIN_STOP, in_place = NU == 0 && (a.flags & FLAG_IN_PLACE);
     const int lane = threadIdx.x & 63;
     const int x = t.x0 - H + lane;
     const bool col = t.live && (unsigned)x < (unsigned)n;
@@ -1900,7 +1913,7 @@ __global__ void __launch_bounds__(256) k_pre_s(StageArgs a)
             }
             {   // smoothed row i - NU (with no sweeps on a zero guess the input rows are zeros)
                 const int r = i - NU;
-                if (own && r >= ylo && r < yhi) B[(size_t)r * ldb + x] = top;
+                if (!in_place && own && r >= ylo && r < yhi) B[(size_t)r * ldb + x] = top;
             }
             Row3<T> Rr;
             {   // residual of row i - NU - 1
@@ -1930,7 +1943,10 @@ __global__ void __launch_bounds__(256) k_pre_s(StageArgs a)
                     const int c = i - NU - 2;
                     if (fwc && c >= ylo && c < yhi) {
                         const int J = (c - 1) >> 1;
-                        if (J < nc) Fc[(size_t)J * ldc + ((x - 1) >> 1)] = acc;
+                        if (J < nc) {
+                            Fc[(size_t)J * ldc + ((x - 1) >> 1)] = acc;
+                            if (in_place) glob<T>(Lc.A)[(size_t)J * Lc.lda + ((x - 1) >> 1)] = T(0);
+                        }
                     }
                     fwp = T(0);
                     fwp += q * Rr.w;
@@ -1962,10 +1978,11 @@ __global__ void __launch_bounds__(256) k_post_s(StageArgs a)
     const LevelDev& Lc = I.lev[d + 1];
     const int n = Lv.n, nc = Lc.n;
     const gp<T> A = glob<T>(Lv.A);
-    const gp<const T> B = glob<T>((const void*)Lv.B);
+    const bool in_place = NU == 0 && (a.flags & FLAG_IN_PLACE);
+    const gp<const T> B = in_place ? (gp<const T>)A : glob<T>((const void*)Lv.B);
     const gp<const T> F = glob<T>((const void*)Lv.F);
     const gp<const T> Vc = glob<T>((const void*)Lc.A);
-    const int lda = Lv.lda, ldf = Lv.ldf, ldb = Lv.ldb, ldc = Lc.lda;
+    const int lda = Lv.lda, ldf = Lv.ldf, ldb = in_place ? Lv.lda : Lv.ldb, ldc = Lc.lda;
     const T fs = (T)Lv.fscale;
     Sten<T> s;
     s.load(Prec<T>::s(I, d));
@@ -4013,13 +4030,9 @@ static hipError_t launch_semi(GridKernel k, const StageArgs& a, int nb, hipStrea
 {
     const dim3 g(nb), b(GRID_THREADS);
     switch (k) {
-    case GK_RESID: k_semi<T, GK_RESID><<<g, b, 0, s>>>(a); break;
-    case GK_RESTRICT: k_semi<T, GK_RESTRICT><<<g, b, 0, s>>>(a); break;
-    case GK_ZERO: k_semi<T, GK_ZERO><<<g, b, 0, s>>>(a); break;
-    case GK_PROLONG: k_semi<T, GK_PROLONG><<<g, b, 0, s>>>(a); break;
-    case GK_ADD: k_semi<T, GK_ADD><<<g, b, 0, s>>>(a); break;
-    case GK_COPY: k_semi<T, GK_COPY><<<g, b, 0, s>>>(a); break;
     case GK_ZERO_SELF: k_semi<T, GK_ZERO_SELF><<<g, b, 0, s>>>(a); break;
+    case GK_SEMI_DOWN: k_semi<T, GK_SEMI_DOWN><<<g, b, 0, s>>>(a); break;
+    case GK_SEMI_UP: k_semi<T, GK_SEMI_UP><<<g, b, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -4116,7 +4129,7 @@ hipError_t launch_grid(GridKernel k, bool f32, const StageArgs& a, int32_t nb, h
     case GK_POSTPRE: e = f32 ? launch_postpre<float>(a, nb, s) : launch_postpre<double>(a, nb, s); break;
     case GK_ZEBRA: e = f32 ? launch_zebra<float>(a, nb, s) : launch_zebra<double>(a, nb, s); break;
     case GK_SWEEP: case GK_RESID: case GK_RESTRICT: case GK_ZERO: case GK_PROLONG: case GK_ADD: case GK_COPY:
-    case GK_NORM: case GK_ZERO_SELF:
+    case GK_NORM: case GK_ZERO_SELF: case GK_SEMI_DOWN: case GK_SEMI_UP:
         if (a.semi && k != GK_NORM && k != GK_SWEEP)
             e = f32 ? launch_semi<float>(k, a, nb, s) : launch_semi<double>(k, a, nb, s);
         else
