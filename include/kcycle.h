@@ -106,8 +106,10 @@ typedef struct {
     int32_t small_tile_n;   /* fused grid kernels on levels whose largest n <= this use 16 x 16 tiles instead of
                                64 x 32 (0 = never; 0..4095; default 511); results do not depend on it */
     int32_t stream_n;       /* fused grid kernels on levels whose largest n >= this stream row strips through
-                               registers instead of staging tiles in LDS (0 = never; default 2047); results do
-                               not depend on it */
+                               registers instead of staging tiles in LDS (0 = never; default 2047).  The next
+                               smaller size too when its tiles are 32 x 32 or larger (the pre-smoothing of FP32
+                               cycles only from two problems' points), and every level where at least four problems
+                               have (stream_n + 1)^2 / 8 points together; results do not depend on it */
     int32_t wave_regs;      /* 1 = whole calls on the levels wave 0 runs alone (n <= coarse_wave_n) run in
                                registers (instances with n_coarsest = 1; default 1); 0 = phase by phase in LDS;
                                results do not depend on it */

@@ -56,6 +56,8 @@ def _shapes(cand: dict, sizes) -> tuple:
         else:
             out.append("64x32")
         n = (n - 1) // 2
+    if stream > 0 and (2 * max(sizes) + 1 >= stream or len(sizes) >= 4):
+        out.append(stream)   # the library also streams some levels below stream_n
     return tuple(out)
 
 

@@ -270,10 +270,11 @@ int zebra_blocks(int lines, int nx, int from, int points)
     return (per_colour + per_block - 1) / per_block;
 }
 int tiles_rect(int nx, int ny) { return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY); }
-// streaming blocks: STRIP_BLOCK_W columns x R rows, R = 16 << code; 32 rows from 2047^2 up for both
-// parts (measured faster than 16 or 64 at 8191^2 and 16383^2); the post-smoothing keeps a shape of its
-// own per depth (shape_post) so that the two parts can take different heights
-int strip_rows_code(int n) { return n >= 2047 ? 1 : 0; }
+// streaming blocks: STRIP_BLOCK_W columns x R rows, R = 16 << code; 32 rows from the points of one 2047^2
+// level up for both parts (measured faster than 16 or 64 at 8191^2 and 16383^2; eight problems on
+// 1023^2, nu = 2, FP64: pre and post 44 and 37 us against 46 and 45 with 16); the post-smoothing has a
+// shape of its own per depth (shape_post)
+int strip_rows_code(int64_t points) { return points >= (1 << 22) ? 1 : 0; }
 int tiles_stream(int n, int code) { return ((n + STRIP_BLOCK_W - 1) / STRIP_BLOCK_W) * ((n + (16 << code) - 1) / (16 << code)); }
 
 // semi: levels coarsened along y only down to one line (every instance the same n)
@@ -922,16 +923,39 @@ kc_status plan_exec(kc_hier* h)
     }
     const int cnt = h->count;
     for (int d = 0; d < MAXL; ++d) {
-        int maxn = 0;
+        int maxn = 0, members = 0;
+        int64_t points = 0;   // with the boundary row and column: a power of two per problem
         for (int i = 0; i < cnt; ++i)
-            if (d < h->hi[i].il.L && h->hi[i].cut > d) maxn = std::max(maxn, h->hi[i].il.n[d]);
+            if (d < h->hi[i].il.L && h->hi[i].cut > d) {
+                maxn = std::max(maxn, h->hi[i].il.n[d]);
+                points += ((int64_t)h->hi[i].il.n[d] + 1) * (h->hi[i].il.n[d] + 1);
+                ++members;
+            }
         int f = 0;
-        if (maxn > 0 && h->ex.stream_n > 0 && maxn >= h->ex.stream_n) f = 2 | (strip_rows_code(maxn) << 2);
+        const int strips = 2 | (strip_rows_code(points) << 2);
+        if (maxn > 0 && h->ex.stream_n > 0 && maxn >= h->ex.stream_n) f = strips;
         else if (maxn > 0 && maxn <= h->ex.tiny_tile_n) f = 32;
         else if (maxn > 0 && maxn <= h->ex.small_tile_n) f = 1;
         else if (maxn > 0 && maxn <= h->ex.mid_tile_n) f = 16;
         h->shape[d] = f;
         h->shape_post[d] = f;
+        // Strips also below stream_n (2047 by default), where they are the faster shape:
+        // - the next smaller size (1023) when it has large tiles: the post-smoothing always (us per launch,
+        //   nu = 2, 32 x 32 tiles / strips: FP64 12.4 / 8.5, FP32 8.5 / 7.4), the pre-smoothing in FP64
+        //   (nu = 1, 2, 3: 10.2, 12.9, 15.6 / 10.1, 11.7, 15.4) and in FP32 (9.0 / 10.2 for one problem)
+        //   from two problems' points (17.1 / 12.6);
+        // - four problems or more with (stream_n + 1)^2 / 8 points on a level: 32 problems on 255 x 255,
+        //   nu = 2, FP64, pre and post, 50 and 46 / 19 and 15.  The tiles' fused sibling calls still win
+        //   below that (kappa = 3 cycles of 1023 x 1023 problems: 511 x 511 in tiles / strips with 2 problems
+        //   269.5 / 270.2 us, 4 329 / 322; 255 x 255 with 4 322 / 327, 8 433 / 407; 127 x 127 with 8 407 / 437,
+        //   32 1036 / 975).
+        const int sn = h->ex.stream_n;
+        if (h->ws && f != strips && maxn > 0 && sn > 0) {
+            const bool next = (f == 0 || f == 16) && 2 * maxn + 1 >= sn;
+            const bool many = members >= 4 && 8 * points >= ((int64_t)sn + 1) * (sn + 1);
+            if (next || many) h->shape_post[d] = strips;
+            if (many || (next && (h->prec == KC_F64 || points >= 2 * ((int64_t)maxn + 1) * (maxn + 1)))) h->shape[d] = strips;
+        }
         int maxl = 0;   // longest line relaxed at this depth
         for (int i = 0; i < cnt; ++i)
             if (d < h->hi[i].il.L && (h->semi || h->hi[i].cut > d)) maxl = std::max(maxl, h->hi[i].il.nx[d]);
