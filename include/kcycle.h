@@ -85,8 +85,8 @@ typedef struct {
     int32_t smoother;   /* 0 = damped Jacobi with omega (default); 1 = alternating zebra line Gauss-Seidel (Section 4,
                            third and fourth solvers): relaxation r of a smoothing step solves every x-line (r even)
                            or y-line (r odd) exactly, lines of even index first, then odd.  In the fused mode
-                           the levels above the coarse cutover run one kernel per operation and every call at
-                           the cutover runs in the persistent kernel (line solves in LDS); in the
+                           the levels above the coarse cutover run one kernel per colour and one for the transfer
+                           each way, and every call at the cutover runs in the persistent kernel; in the
                            paper-structured mode every level runs one kernel per operation.  Needs n <= 16383
                            (else KC_ERR_ARG) */
     double omega;

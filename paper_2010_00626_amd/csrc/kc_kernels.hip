@@ -726,7 +726,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_semi(StageArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// zebra line relaxation on the levels run one kernel per operation: every line of the launch's
+// zebra line relaxation on the levels above the persistent kernel's: every line of the launch's
 // colour (lines 2 m + colour) solves its tridiagonal system exactly with its
 // neighbouring lines' current values, in place.  Forward pass:
 // d_q = F_q - (six off-line products: line j-1 then j+1, west to east, for

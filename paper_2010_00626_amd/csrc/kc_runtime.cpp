@@ -416,7 +416,7 @@ void gen_sub_call(const HostInst& h, int d, int k, bool zg, int reg_n, std::vect
 struct kc_hier {
     int count = 0;
     kc_precision prec = KC_F64;
-    bool semi = false;   // levels coarsened along y only (x-line zebra, one kernel per operation)
+    bool semi = false;   // levels coarsened along y only (x-line zebra; one kernel per colour and per transfer)
     kc_exec ex{};
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -1784,7 +1784,7 @@ static kc_status create_impl(const kc_problem* probs, int32_t count, kc_precisio
     h->semi = semi;
     kc_exec_default(&h->ex);
     if (exec) h->ex = *exec;
-    if (semi) h->ex.mode = 1;   // one kernel per operation on the rectangular levels
+    if (semi) h->ex.mode = 1;   // grid kernels on every rectangular level (none in the persistent kernel)
     kc_status s = validate_exec(&h->ex, (int)prec);
     if (s != KC_OK) { delete h; return s; }
     s = make_layout(probs, count, prec, h->lay, semi);
