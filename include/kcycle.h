@@ -97,9 +97,10 @@ typedef struct {
     int32_t mode;           /* 0 = fused kernels + persistent coarse subtree (default);
                                1 = one kernel per operation of Algorithm 4 ("paper-structured") */
     int32_t use_graph;      /* 1 = capture one cycle as a hipGraph and replay it (default) */
-    int32_t coarse_cutover; /* levels with n <= cutover run in the persistent kernel (7..63; default 31, which a plan
-                               of up to 256 instances with n_coarsest 1 or 3 and the other defaults raises to 63:
-                               faster, and results do not depend on it; kc_schedule_counts takes it as given) */
+    int32_t coarse_cutover; /* levels with n <= cutover run in the persistent kernel (7..63; default 0 = the plan
+                               chooses: 63 for up to 256 instances of one n_coarsest, 1 or 3, with the persistent
+                               kernel's other options at their defaults, else 31; kc_stats names the one planned);
+                               results do not depend on it */
     int32_t coarse_threads; /* threads of the persistent kernel (256, 512, or 1024 with FP32 cycles; default 512) */
     int32_t poll_every;     /* cycles launched between host polls of the stop flags (default 0 = adaptive) */
     int32_t coarse_wave_n;  /* persistent-kernel levels with n <= this run on one wave (0..15; default 15) */

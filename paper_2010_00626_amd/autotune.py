@@ -36,10 +36,10 @@ DEFAULT_STAGES = (tuple(dict(coarse_cutover=31, coarse_threads=512, coarse_wave_
 
 
 def _shapes(cand: dict, sizes) -> tuple:
-    """Kernel shape of every level above the coarse cutover of a hierarchy with
-    the given fine sizes (largest n per depth), as the library picks it: two
-    candidates with the same shapes give the same schedule."""
-    cut = cand.get("coarse_cutover", 31)
+    """Kernel shape of every level above the candidate's coarse cutover of a
+    hierarchy with the given fine sizes (largest n per depth), as the library
+    picks it: two candidates with the same shapes give the same schedule."""
+    cut = cand["coarse_cutover"]
     small, mid, stream = cand.get("small_tile_n", 511), cand.get("mid_tile_n", 2047), cand.get("stream_n", 2047)
     tiny = cand.get("tiny_tile_n", 0)
     out = []
@@ -64,7 +64,7 @@ def _shapes(cand: dict, sizes) -> tuple:
 def _relevant(cand: dict, seen: set, sizes) -> bool:
     """Skip a candidate whose per-level kernel shapes (and persistent-kernel
     options) equal those of one already tried."""
-    key = (_shapes(cand, sizes), cand.get("coarse_cutover", 31), cand.get("coarse_threads", 512),
+    key = (_shapes(cand, sizes), cand["coarse_cutover"], cand.get("coarse_threads", 512),
            cand.get("coarse_wave_n", 15))
     if key in seen:
         return False
@@ -131,6 +131,12 @@ def tune(H: "kcycle.Hierarchy", u, f, kappa: int, nu1: int = 2, nu2: int = 2, om
             stage = tuple({k: t["exec"][k] for k in tile_keys if k in t["exec"]} for t in first)
         for part in stage:
             cand = dict(base, **part)
+            if not cand.get("coarse_cutover"):    # the cutover that the library plans for these options
+                try:
+                    H.set_exec(**cand)
+                except kcycle.KCycleError:
+                    continue
+                cand["coarse_cutover"] = H.stats()["coarse_cutover"]
             if not _relevant(cand, seen, H.sizes):
                 continue
             try:

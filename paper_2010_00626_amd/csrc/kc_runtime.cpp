@@ -830,19 +830,18 @@ kc_status build_tables(kc_hier* h, const std::vector<char>* active)
     return KC_OK;
 }
 
-// The register kernel runs a call on 63 x 63 in less time than the two grid launches around a call on
-// 31 x 31 take (per cycle, FP64 1023^2, kappa = 1, 2, 3: 65.9, 162, 282 us against 67.2, 170, 305; 16
-// problems in FP32, kappa = 3: 836 against 895 us), so a hierarchy planned on the GPU with the default
-// cutover of 31 takes 63 where that kernel runs its coarse levels and every instance can have a CU
-int effective_cutover(const kc_hier* h)
+// the cutover of a plan: the option, or for the automatic choice (0) 63 where the register kernel runs the
+// coarse levels and every instance can have a CU, else 31.  That kernel runs a call on 63 x 63 in less time
+// than the two grid launches around a call on 31 x 31 take (per cycle, FP64 1023^2, kappa = 1, 2, 3: 65.9,
+// 162, 282 us against 67.2, 170, 305; 16 problems in FP32, kappa = 3: 836 against 895 us)
+int planned_cutover(const kc_hier* h)
 {
     const kc_exec& e = h->ex;
-    if (!h->ws || h->semi || e.mode != 0 || e.coarse_cutover != 31 || e.coarse_threads < 512 || !e.wave_regs ||
-        e.coarse_wave_n != 15 || h->count > 256)
-        return e.coarse_cutover;
+    if (e.coarse_cutover != 0) return e.coarse_cutover;
+    if (h->semi || e.mode != 0 || e.coarse_threads < 512 || !e.wave_regs || e.coarse_wave_n != 15 || h->count > 256) return 31;
     const int nc = h->hi[0].p.n_coarsest;
     for (const HostInst& hi : h->hi)
-        if (hi.p.n_coarsest != nc || nc > 3) return e.coarse_cutover;
+        if (hi.p.n_coarsest != nc || nc > 3) return 31;
     return 63;
 }
 
@@ -852,7 +851,7 @@ int effective_cutover(const kc_hier* h)
 kc_status plan_exec(kc_hier* h)
 {
     const size_t T = (h->prec == KC_F64) ? 8 : 4;
-    const int cutover = effective_cutover(h);
+    const int cutover = planned_cutover(h);
     h->max_cut = 0;
     h->max_L = 0;
     h->sub_lds = 0;
@@ -1549,7 +1548,7 @@ void kc_exec_default(kc_exec* e)
     std::memset(e, 0, sizeof *e);
     e->mode = 0;
     e->use_graph = 1;
-    e->coarse_cutover = 31;
+    e->coarse_cutover = 0;
     e->coarse_threads = 512;
     e->poll_every = 0;
     e->coarse_wave_n = 15;
@@ -1656,7 +1655,8 @@ kc_status kc_convection_stencils(const kc_problem* p, double bx, double by, int3
 static kc_status validate_exec(const kc_exec* e, int prec)
 {
     if (e->mode != 0 && e->mode != 1) return fail(KC_ERR_ARG, "exec.mode must be 0 or 1");
-    if (e->coarse_cutover < 7 || e->coarse_cutover > 63) return fail(KC_ERR_ARG, "coarse_cutover must be in 7..63");
+    if (e->coarse_cutover != 0 && (e->coarse_cutover < 7 || e->coarse_cutover > 63))
+        return fail(KC_ERR_ARG, "coarse_cutover must be in 7..63, or 0 for the automatic choice");
     if (e->coarse_threads != 256 && e->coarse_threads != 512 && e->coarse_threads != 1024)
         return fail(KC_ERR_ARG, "coarse_threads must be 256, 512 or 1024");
     if (e->coarse_threads == 1024 && prec == (int)KC_F64)
@@ -2312,7 +2312,7 @@ kc_status kc_stats(const kc_hier* h, char* out, size_t cap)
     js += ", \"precision\": \"" + std::string(h->prec == KC_F64 ? "f64" : "f32_cycle") + "\"";
     js += ", \"mode\": \"" + std::string(h->ex.mode == 1 ? "paper" : "fused") + "\"";
     js += ", \"graph\": " + std::to_string(h->ex.use_graph);
-    js += ", \"coarse_cutover\": " + std::to_string(h->ex.coarse_cutover);
+    js += ", \"coarse_cutover\": " + std::to_string(planned_cutover(h));
     js += ", \"coarse_threads\": " + std::to_string(h->ex.coarse_threads);
     js += ", \"coarse_wave_n\": " + std::to_string(h->ex.coarse_wave_n);
     js += ", \"small_tile_n\": " + std::to_string(h->ex.small_tile_n);

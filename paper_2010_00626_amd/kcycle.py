@@ -113,7 +113,7 @@ def _check(status: int, allow_positive: bool = False) -> int:
     return status
 
 
-def exec_options(mode: int | str = 0, use_graph: bool = True, coarse_cutover: int = 31,
+def exec_options(mode: int | str = 0, use_graph: bool = True, coarse_cutover: int = 0,
                  coarse_threads: int = 512, poll_every: int = 0, coarse_wave_n: int = 15,
                  small_tile_n: int = 511, stream_n: int = 2047, wave_regs: int = 1,
                  fuse_junctions: int = 1, mid_tile_n: int = 2047, tiny_tile_n: int = 255,
