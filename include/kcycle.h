@@ -101,7 +101,8 @@ typedef struct {
                                chooses: 63 for up to 256 instances of one n_coarsest, 1 or 3, with the persistent
                                kernel's other options at their defaults, else 31; kc_stats names the one planned);
                                results do not depend on it */
-    int32_t coarse_threads; /* threads of the persistent kernel (256, 512, or 1024 with FP32 cycles; default 512) */
+    int32_t coarse_threads; /* threads of the persistent kernel (256, 512, or 1024 with FP32 cycles; default 512, of
+                               which the calls that run wholly in registers take 64 to 512: see wave_regs) */
     int32_t poll_every;     /* cycles launched between host polls of the stop flags (default 0 = adaptive) */
     int32_t coarse_wave_n;  /* persistent-kernel levels with n <= this run on one wave (0..15; default 15) */
     int32_t small_tile_n;   /* fused grid kernels on levels whose largest n <= this use 16 x 16 tiles instead of
@@ -112,8 +113,10 @@ typedef struct {
                                cycles only from two problems' points), and every level where at least four problems
                                have (stream_n + 1)^2 / 8 points together; results do not depend on it */
     int32_t wave_regs;      /* 1 = whole calls on the levels wave 0 runs alone (n <= coarse_wave_n) run in
-                               registers (instances with n_coarsest = 1; default 1); 0 = phase by phase in LDS;
-                               results do not depend on it */
+                               registers (instances with n_coarsest = 1; default 1); 0 = phase by phase in LDS.
+                               With coarse_wave_n 15 and coarse_threads 512 a damped-Jacobi call keeps every level
+                               in registers where its instances share a top level of 15, 31 or 63 points a side
+                               and an n_coarsest of 1 or 3; results do not depend on it */
     int32_t fuse_junctions; /* 1 = on levels run in 8 x 8 or 16 x 16 tiles, the post-smoothing of a call's first child and the
                                pre-smoothing of its second child (kappa >= 2) run as one kernel (default 1); results
                                do not depend on it */

@@ -514,12 +514,16 @@ Launch fused_grid(kc_hier* h, GridKernel gk, bool f32, int d)
     return L;
 }
 
+// whether the plan's options leave the register kernel its calls (a thread count other than the default asks
+// for k_subtree with that many)
+bool regs_options(const kc_exec& e) { return e.wave_regs && e.coarse_wave_n == 15 && e.coarse_threads == 512; }
+
 // whether the register kernel runs the calls at this depth (damped Jacobi down to a 1 x 1 or 3 x 3 level,
 // instances of one size): sets the launch's level sizes, else k_subtree runs them
 void set_regs(const kc_hier* h, int depth, int smoother, SubArgs& a)
 {
     a.regs = a.coarsest = 0;
-    if (smoother != 0 || !h->ex.wave_regs || h->ex.coarse_wave_n != 15 || h->lists[lt_sub(depth)].empty()) return;
+    if (smoother != 0 || !regs_options(h->ex) || h->lists[lt_sub(depth)].empty()) return;
     const HostInst& first = h->hi[h->lists[lt_sub(depth)][0]];
     const int n = first.il.n[depth], nc = first.p.n_coarsest;
     if ((n != 15 && n != 31 && n != 63) || (nc != 1 && nc != 3)) return;
@@ -838,7 +842,7 @@ int planned_cutover(const kc_hier* h)
 {
     const kc_exec& e = h->ex;
     if (e.coarse_cutover != 0) return e.coarse_cutover;
-    if (h->semi || e.mode != 0 || e.coarse_threads < 512 || !e.wave_regs || e.coarse_wave_n != 15 || h->count > 256) return 31;
+    if (h->semi || e.mode != 0 || !regs_options(e) || h->count > 256) return 31;
     const int nc = h->hi[0].p.n_coarsest;
     for (const HostInst& hi : h->hi)
         if (hi.p.n_coarsest != nc || nc > 3) return 31;

@@ -15,7 +15,8 @@ def counts(problems, **ex):
 @pytest.mark.parametrize("problems,ex,planned", [
     (P1023, {}, 63), ([(255, 0.4, 1e-3, 3)] * 256, {}, 63), ([(511, 0.4, 1e-3), (127, 1.0, 1e-2)], {}, 63),
     ([(1023, 0.4, 1e-3, 7)], {}, 31), ([(255, 0.4, 1e-3)] * 257, {}, 31), ([(255, 0.4, 1e-3, 3), (255, 0.4, 1e-3, 1)], {}, 31),
-    (P1023, dict(wave_regs=0), 31), (P1023, dict(coarse_wave_n=7), 31), (P1023, dict(coarse_threads=256), 31)])
+    (P1023, dict(wave_regs=0), 31), (P1023, dict(coarse_wave_n=7), 31), (P1023, dict(coarse_threads=256), 31),
+    (P1023, dict(coarse_threads=1024), 31)])
 def test_automatic_cutover(problems, ex, planned):
     assert counts(problems, **ex) == counts(problems, coarse_cutover=planned, **ex)
     other = 31 if planned == 63 and not ex else 15
@@ -75,4 +76,31 @@ def test_tuner_plans_what_it_times():
                         stages=((dict(tiny_tile_n=255), dict(tiny_tile_n=0), dict(coarse_cutover=63), dict(coarse_cutover=31)),))
     assert sorted(t["exec"]["coarse_cutover"] for t in res["trials"]) == [31, 63, 63]
     assert H.stats()["coarse_cutover"] == res["exec"]["coarse_cutover"]
+    H.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,ex,kernel", [
+    ("f32", dict(coarse_cutover=63, coarse_threads=1024), "k_subtree<float, 1024, false>"),
+    ("f32", dict(coarse_cutover=31, coarse_threads=1024), "k_subtree<float, 1024, false>"),
+    ("f32", dict(coarse_cutover=31, coarse_threads=256), "k_subtree<float, 256, false>"),
+    ("f64", dict(coarse_cutover=15, coarse_threads=256), "k_subtree<double, 256, false>"),
+    ("f32", dict(coarse_cutover=63, wave_regs=0), "k_subtree<float, 512, false>"),
+    ("f64", dict(coarse_cutover=31, coarse_wave_n=7), "k_subtree<double, 512, false>"),
+    ("f32", dict(coarse_cutover=31), "k_subtree_regs<float, 31, 4, 1>")])
+def test_threads_are_honoured(prec, ex, kernel):
+    """The kernel asked for runs, and its step is the oracle's (FP32: its emulation) bit for bit."""
+    from oracle import oracle as O
+    import torch
+    n = 127
+    print(f"[coarse-options] {prec} {ex}", flush=True)
+    f = np.random.default_rng(5).uniform(-1, 1, (n, n))
+    Ho = O.Hierarchy(n, 0.9, 1e-2)
+    ref = (Ho.ir_solve if prec == "f32" else Ho.solve)(f, kappa=3, tol=1e-300, maxit=1)[0]
+    H = K.Hierarchy([(n, 0.9, 1e-2)], prec, exec=ex)
+    u = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+    it, rr, st = H.solve(u, torch.from_numpy(f).cuda(), kappa=3, tol=1e-300, maxit=1)
+    assert it == [1] and np.array_equal(u.cpu().numpy(), ref)
+    names = [k["name"] for k in H.profile_iteration(kappa=3, reps=1)["kernels"]]
+    assert [x for x in names if x.startswith("k_subtree")] == [kernel], names
     H.close()
