@@ -3059,12 +3059,19 @@ __device__ __forceinline__ double bperm(int addr, double x)
 constexpr int DPP_ROW_SHR4 = 0x114, DPP_ROW_SHL4 = 0x104;   // values of lane - 4 / lane + 4 (0 outside the 16 lanes)
 
 // a / b, correctly rounded, from y = 1 / b (Markstein 1990: a correction with the exact remainder rounds a
-// quotient correctly once it is within a unit in the last place; the first step brings it there).  Quotients
-// whose remainder could leave the normal range are divided.
+// quotient correctly once it is within a unit in the last place; the first step brings it there).  That needs
+// a remainder (a's exponent less twice the significand's bits) and a quotient in the normal range: dividends
+// outside div_ok are divided, and a divisor that could take a quotient out of it has no reciprocal (NaN, which
+// the dividends after it carry to div_ok).
 template <typename T> __device__ __forceinline__ bool div_ok(T a)
 {
-    const T lim = sizeof(T) == 8 ? T(0x1p900) : T(0x1p100);
-    return fabs(a) > T(1) / lim && fabs(a) < lim;
+    const T low = sizeof(T) == 8 ? T(0x1p-900) : T(0x1p-78), high = sizeof(T) == 8 ? T(0x1p900) : T(0x1p100);
+    return fabs(a) > low && fabs(a) < high;
+}
+template <typename T> __device__ __forceinline__ T div_recip(T b)
+{
+    const T lim = sizeof(T) == 8 ? T(0x1p100) : T(0x1p20);
+    return b > T(1) / lim && b < lim ? T(1) / b : T(NAN);
 }
 template <typename T> __device__ __forceinline__ T div_fast(T a, T b, T y)
 {
@@ -3530,13 +3537,13 @@ __global__ void __launch_bounds__(64 * W) k_subtree_regs(SubArgs a)
         if (tid == 64 * W - 1) {
             const T l = ch[0];
             L.chol[0] = l;
-            L.chol[1] = T(1) / l;
+            L.chol[1] = div_recip(l);
         }
     } else {
         for (int p = tid; p < 81; p += 64 * W) {
             const T l = ch[p];
             L.chol[p] = l;
-            if (p % 10 == 0) L.chol[81 + p / 10] = T(1) / l;
+            if (p % 10 == 0) L.chol[81 + p / 10] = div_recip(l);
         }
     }
     if constexpr (N == 63)
