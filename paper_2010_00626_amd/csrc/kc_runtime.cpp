@@ -340,15 +340,16 @@ kc_status make_layout(const kc_problem* probs, int count, kc_precision prec, Lay
             il.zoff[d] = zt;
             zt += 4 * (size_t)il.nx[d];
         }
-        il.zt64 = take(sizeof(double) * zt);
-        il.zt32 = take(sizeof(float) * zt);
+        const bool f64 = prec == KC_F64;   // line-solve tables in the precision of the cycles
+        il.zt64 = take(f64 ? sizeof(double) * zt : 0);
+        il.zt32 = take(f64 ? 0 : sizeof(float) * zt);
         size_t zl = 0;   // lane-order copies, n + 1 entries per table (a multiple of 16 bytes)
         for (int d = 0; d < il.L; ++d) {
             il.zloff[d] = zl;
             if (il.nx[d] >= ZREG_N) zl += 4 * (size_t)(il.nx[d] + 1);
         }
-        il.zl64 = take(sizeof(double) * zl);
-        il.zl32 = take(sizeof(float) * zl);
+        il.zl64 = take(f64 ? sizeof(double) * zl : 0);
+        il.zl32 = take(f64 ? 0 : sizeof(float) * zl);
         const size_t v64 = (size_t)il.n[0] * il.ld[0] * 8;
         il.r = take(v64);
         il.z = take(v64);
@@ -1057,10 +1058,13 @@ void fill_inst_static(kc_hier* h)
         I.chol64 = (const double*)(h->ws + hi.il.chol64);
         I.chol32 = (const float*)(h->ws + hi.il.chol32);
         for (int d = 0; d < hi.il.L; ++d) {
-            I.zt64[d] = (const double*)(h->ws + hi.il.zt64) + hi.il.zoff[d];
-            I.zt32[d] = (const float*)(h->ws + hi.il.zt32) + hi.il.zoff[d];
-            I.zl64[d] = (const double*)(h->ws + hi.il.zl64) + hi.il.zloff[d];
-            I.zl32[d] = (const float*)(h->ws + hi.il.zl32) + hi.il.zloff[d];
+            if (f64) {
+                I.zt64[d] = (const double*)(h->ws + hi.il.zt64) + hi.il.zoff[d];
+                I.zl64[d] = (const double*)(h->ws + hi.il.zl64) + hi.il.zloff[d];
+            } else {
+                I.zt32[d] = (const float*)(h->ws + hi.il.zt32) + hi.il.zoff[d];
+                I.zl32[d] = (const float*)(h->ws + hi.il.zl32) + hi.il.zloff[d];
+            }
         }
         I.r = (double*)(h->ws + hi.il.r);
         I.z = (double*)(h->ws + hi.il.z);
