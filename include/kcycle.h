@@ -264,8 +264,12 @@ kc_status kc_convection_stencils(const kc_problem* p, double bx, double by, int3
 kc_status kc_level_stencils(const kc_problem* p, int32_t max_levels, int32_t* nlevels, double* stencils);
 
 /* host-only: the flattened stage schedule of one cycle, as launches per cycle
- * (grid kernels, persistent-kernel launches, persistent-kernel stages);
- * no GPU needed */
+ * (grid kernels, persistent-kernel launches, persistent-kernel stages) of an
+ * FP64 hierarchy; no GPU needed.  Two things are counted that a hierarchy runs
+ * otherwise: with the zebra smoother, the five operations between a level's
+ * relaxation and its coarse calls one by one (two launches run outside the
+ * paper-structured mode), and as stages the operations of k_subtree's lists
+ * (calls in the register kernel are one launch without a list) */
 kc_status kc_schedule_counts(const kc_problem* probs, int32_t count, const kc_exec* exec,
                              const kc_cycle_params* c, int64_t* grid_launches, int64_t* subtree_launches,
                              int64_t* subtree_stages);

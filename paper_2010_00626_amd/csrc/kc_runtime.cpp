@@ -706,7 +706,7 @@ void gen_paper(kc_hier* h, int d, int k, const kc_cycle_params& c, bool f32, int
     // zebra relaxation works in place, so the operations between it and the coarse calls run as one launch
     // each way: at 4095 x 4095 60 + 62 us instead of 180 + 147 us (five passes over memory), on the small
     // levels two launches instead of five.  Not in the paper-structured mode, whose point is one kernel per
-    // operation, nor in host-only planning, which lists every operation.
+    // operation, nor in host-only planning (kc_schedule_counts), which counts every operation.
     const bool fuse = h->ws && c.smoother == 1 && (hybrid || h->semi);
     auto transfer = [&](GridKernel full, GridKernel semi) {
         if (h->semi) {
@@ -954,7 +954,7 @@ kc_status plan_exec(kc_hier* h)
         //   269.5 / 270.2 us, 4 329 / 322; 255 x 255 with 4 322 / 327, 8 433 / 407; 127 x 127 with 8 407 / 437,
         //   32 1036 / 975).
         const int sn = h->ex.stream_n;
-        if (h->ws && f != strips && maxn > 0 && sn > 0) {
+        if (f != strips && maxn > 0 && sn > 0) {
             const bool next = (f == 0 || f == 16) && 2 * maxn + 1 >= sn;
             const bool many = members >= 4 && 8 * points >= ((int64_t)sn + 1) * (sn + 1);
             if (next || many) h->shape_post[d] = strips;

@@ -104,3 +104,30 @@ def test_threads_are_honoured(prec, ex, kernel):
     names = [k["name"] for k in H.profile_iteration(kappa=3, reps=1)["kernels"]]
     assert [x for x in names if x.startswith("k_subtree")] == [kernel], names
     H.close()
+
+
+def test_counts_of_streamed_levels():
+    """Levels that a batch streams below stream_n have no fused sibling launches, in the counts too."""
+    four = [(1023, 0.4, 1e-3)] * 4
+    assert counts(four) == counts(four, stream_n=0, small_tile_n=0, mid_tile_n=4095)
+    assert counts(four) != counts(four, stream_n=0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("problems,ex,smoother", [
+    ([(1023, 0.4, 1e-3)], {}, "jacobi"), ([(1023, 0.4, 1e-3)] * 4, {}, "jacobi"), ([(255, 0.4, 1e-3, 7)], {}, "jacobi"),
+    ([(255, 0.4, 1e-3)], dict(coarse_cutover=31), "jacobi"), ([(255, 0.4, 1e-3)], dict(mode="paper"), "zebra"),
+    ([(255, 0.4, 1e-3)], {}, "zebra")])
+def test_counts_are_the_launches(problems, ex, smoother):
+    import torch
+    print(f"[coarse-options] counts {problems[0]} x {len(problems)} {ex} {smoother}", flush=True)
+    c = K.schedule_counts(problems, 2, smoother=smoother, **ex)
+    H = K.Hierarchy(problems, exec=ex)
+    v = [torch.zeros((p[0], p[0]), dtype=torch.float64, device="cuda") for p in problems]
+    H.cycle(v, [torch.ones_like(t) for t in v], kappa=2, smoother=smoother)
+    s = H.stats()
+    # zebra in the fused mode: three launches fewer per call above the cutover (one call on 255, two on 127)
+    fewer = 3 * 3 if smoother == "zebra" and not ex else 0
+    assert s["grid_launches_per_iteration"] == c["grid_launches"] - fewer
+    assert s["subtree_launches_per_iteration"] == c["subtree_launches"]
+    H.close()
