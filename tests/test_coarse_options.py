@@ -86,6 +86,8 @@ def test_tuner_plans_what_it_times():
     ("f32", dict(coarse_cutover=31, coarse_threads=256), "k_subtree<float, 256, false>"),
     ("f64", dict(coarse_cutover=15, coarse_threads=256), "k_subtree<double, 256, false>"),
     ("f32", dict(coarse_cutover=63, wave_regs=0), "k_subtree<float, 512, false>"),
+    ("f32", dict(coarse_cutover=31, wave_regs=0), "k_subtree<float, 512, false>"),
+    ("f64", dict(coarse_cutover=63, wave_regs=0), "k_subtree<double, 512, false>"),
     ("f64", dict(coarse_cutover=31, coarse_wave_n=7), "k_subtree<double, 512, false>"),
     ("f32", dict(coarse_cutover=31), "k_subtree_regs<float, 31, 4, 1>")])
 def test_threads_are_honoured(prec, ex, kernel):
