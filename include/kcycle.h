@@ -125,7 +125,7 @@ typedef struct {
     int32_t tiny_tile_n;    /* fused grid kernels on levels whose largest n <= this use 8 x 8 tiles (one point per
                                thread and phase; takes precedence over small_tile_n; 0 = never; 0..4095; default 255);
                                results do not depend on it */
-    int32_t zebra_wave_n;   /* zebra line relaxation on levels with n >= this (and at least 63) keeps lines in the
+    int32_t zebra_wave_n;   /* zebra line relaxation on levels with n >= this (and at least 3) keeps lines in the
                                registers of up to 64 lanes each; smaller levels use one thread per line (0 = never;
                                0..16383; default 63); results do not depend on it */
     int32_t zebra_quad_n;   /* of those levels, the ones with n >= this give a y-line 32 lanes instead of 64 (twice as

@@ -21,7 +21,7 @@ constexpr int TT = 8;             // tiny tile side of the fused kernels (one po
 constexpr int STRIP_BLOCK_W = 216; // columns of a streaming block (4 strips of 54)
 constexpr int FLAG_IN_PLACE = 64; // fused kernels without sweeps: estimate in place on A, coarse estimate set to zero
 constexpr int GRID_THREADS = 256; // threads of the grid-wide kernels
-constexpr int ZREG_N = 63;        // zebra line kernel: shortest line of the registers mapping
+constexpr int ZREG_N = 3;         // zebra line kernel: shortest line of the registers mapping (four points per lane)
 // points per lane of that mapping, from the longest line of a launch
 inline int zebra_points(int n) { return n <= 255 ? 4 : n <= 511 ? 8 : 16; }
 // most lanes per line (log2) along direction dir (0 x, 1 y)

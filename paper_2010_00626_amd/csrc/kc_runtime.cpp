@@ -259,14 +259,15 @@ int lg_of(int n)
     return lg;
 }
 
-// zebra launches: an instance takes the registers mapping from this line length (0: never)
+// zebra launches: an instance takes the registers mapping from this line length (0: never), if its line
+// fills a lane of the launch (the longest line gives the points per lane)
 int zebra_from(const kc_exec& e) { return e.zebra_wave_n > 0 ? std::max(e.zebra_wave_n, ZREG_N) : 0; }
 // blocks of one colour's lines of one instance: GRID_THREADS threads with (nx + 1) / points lanes per
 // line, 64 at most, in the registers mapping, else one thread per line (64 per block)
 int zebra_blocks(int lines, int nx, int from, int points)
 {
     const int per_colour = (lines + 1) / 2;
-    const int per_block = from > 0 && nx >= from ? GRID_THREADS / std::min((nx + 1) / points, 64) : 64;
+    const int per_block = from > 0 && nx >= from && nx + 1 >= points ? GRID_THREADS / std::min((nx + 1) / points, 64) : 64;
     return (per_colour + per_block - 1) / per_block;
 }
 int tiles_rect(int nx, int ny) { return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY); }
