@@ -20,6 +20,7 @@ constexpr int TM = 32;            // mid-level tile side of the fused kernels
 constexpr int TT = 8;             // tiny tile side of the fused kernels (one point per thread and phase)
 constexpr int STRIP_BLOCK_W = 216; // columns of a streaming block (4 strips of 54)
 constexpr int FLAG_IN_PLACE = 64; // fused kernels without sweeps: estimate in place on A, coarse estimate set to zero
+constexpr int FLAG_TO_A = 128;    // pre-smoothing on a zero guess: estimate to A, where the sibling junction reads it
 constexpr int GRID_THREADS = 256; // threads of the grid-wide kernels
 constexpr int ZREG_N = 3;         // zebra line kernel: shortest line of the registers mapping (four points per lane)
 // points per lane of that mapping, from the longest line of a launch
@@ -228,7 +229,8 @@ enum GridKernel : int32_t {
     GK_APPLY = 19,     // y = S x / h^2
     GK_GRAD = 20,      // -lam^T dS u / h^2 for theta and eps
     GK_ZERO_SELF = 22, // unfused: A[d] = 0 on the launch's own level
-    GK_POSTPRE = 23,   // fused junction of sibling calls: post (nu2 = src) of the first + pre (nu) of the second
+    GK_POSTPRE = 23,   // fused junction of sibling calls: post (nu2 = src) of the first, whose estimate is in A
+                       // (FLAG_TO_A), + pre (nu) of the second, whose estimate goes to B
     GK_ZEBRA = 24,     // zebra line relaxation in place on buffer src, lines of colour dst, direction nu (0 x, 1 y); zg and
                        // flags: zebra_args
     GK_SEMI_DOWN = 26, // semi-coarsened: residual of A, F[d+1] = R r, A[d+1] = 0

@@ -1349,7 +1349,9 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     const Tile t = tile_at<TX, TY>(blk, n);
     const int done = a.st[inst].done;
     const gp<const T> A = glob<T>((const void*)Lv.A);
-    const gp<T> B = glob<T>(Lv.B);
+    const bool to_a = a.flags & FLAG_TO_A;   // on a zero guess, which reads no estimate
+    const gp<T> B = glob<T>(to_a ? Lv.A : Lv.B);
+    const int ldb = to_a ? Lv.lda : Lv.ldb;
     const gp<const T> F = glob<T>((const void*)Lv.F);
     const T fs = (T)Lv.fscale;
     const int rx0 = t.x0 - H, ry0 = t.y0 - H;
@@ -1428,7 +1430,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     for (int p = threadIdx.x; p < (in_place ? 0 : TX * TY); p += GRID_THREADS) {
         const int y = p / TX, x = p % TX;
         const int j = t.y0 + y, i = t.x0 + x;
-        if (j < n && i < n) B[(size_t)j * Lv.ldb + i] = vs[(H + y) * RW + (H + x)];
+        if (j < n && i < n) B[(size_t)j * ldb + i] = vs[(H + y) * RW + (H + x)];
     }
     // residual on [x0, x0+TX] x [y0, y0+TY]
     if constexpr (TX == TY && TX <= 32) {
@@ -1567,9 +1569,10 @@ __global__ void __launch_bounds__(GRID_THREADS) k_post(StageArgs a)
 // fused junction of two sibling calls on one level (kappa >= 2): the first
 // call's prolong-add + NU2 sweeps and the second call's NU1 sweeps + residual +
 // full weighting, in one tile kernel.  The first call's result would be
-// written to A only for the second call's pre-smoothing to read it back, so it
-// stays in LDS; the input is the first call's pre-smoothed estimate (B), the
+// written only for the second call's pre-smoothing to read it back, so it
+// stays in LDS; the input is the first call's pre-smoothed estimate, in A, the
 // output goes to B and F of the coarse level, as the pre-smoothing writes them.
+// Tiles read their neighbours' points, so input and output are two buffers.
 // Input region = tile + halo NU2 + NU1 + 1 (+1 on the high side for the
 // residual ring of the full weighting).
 // ---------------------------------------------------------------------------
@@ -1591,6 +1594,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_postpre(StageArgs a)
     const Tile t = tile_at<TX, TY>(blk, Lv.n);
     const int done = a.st[inst].done;
     const int n = Lv.n, nc = Lc.n;
+    const gp<const T> A = glob<T>((const void*)Lv.A);   // read with a halo, so the result goes to the other buffer
     const gp<T> B = glob<T>(Lv.B);
     const gp<const T> F = glob<T>((const void*)Lv.F);
     const gp<const T> Vc = glob<T>((const void*)Lc.A);
@@ -1614,7 +1618,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_postpre(StageArgs a)
             const bool in = p < NR && inside(j, i, n);
             const size_t jc = (size_t)clampi(j, n), ic = (size_t)clampi(i, n);
             const T lf = F[jc * Lv.ldf + ic];
-            const T lv = B[jc * Lv.ldb + ic];
+            const T lv = A[jc * Lv.lda + ic];
             fa[k] = in ? fs * lf : T(0);
             va[k] = in ? lv : T(0);
         }

@@ -614,7 +614,9 @@ void gen_fused(kc_hier* h, int d, int k, bool zg, int fin, const kc_cycle_params
 }
 
 // a post-smoothing launch followed by the pre-smoothing of the next sibling call on the same
-// level (16 x 16 tiles) becomes one fused junction launch
+// level (16 x 16 or 8 x 8 tiles) becomes one fused junction launch.  A junction's tiles read their
+// neighbours' points, so it must not write where it reads: the first call's pre-smoothing, on a
+// zero guess, puts its estimate in A instead of B, and the junction goes from A to B
 void fuse_junctions(std::vector<Launch>& ls, size_t from)
 {
     std::vector<Launch> out(ls.begin(), ls.begin() + from);
@@ -626,6 +628,16 @@ void fuse_junctions(std::vector<Launch>& ls, size_t from)
                 L.sa.depth == M.sa.depth && L.sa.tile_off == M.sa.tile_off && (L.sa.flags == 1 || L.sa.flags == 32) &&
                 M.sa.flags == L.sa.flags &&
                 M.sa.zg == 0 && M.sa.fin == FIN_NONE && L.sa.fin == FIN_NONE) {
+                // the first call's pre-smoothing: the last one at this depth
+                size_t p = out.size();
+                while (p > from && !(out[p - 1].type == L_GRID && out[p - 1].sa.depth == L.sa.depth &&
+                                     (out[p - 1].gk == GK_PRE || out[p - 1].gk == GK_POSTPRE)))
+                    --p;
+                if (p == from || out[p - 1].gk != GK_PRE || !out[p - 1].sa.zg || out[p - 1].sa.flags != L.sa.flags) {
+                    out.push_back(L);
+                    continue;
+                }
+                out[p - 1].sa.flags |= FLAG_TO_A;
                 Launch F = M;
                 F.gk = GK_POSTPRE;
                 F.sa.src = L.sa.nu;   // nu2 of the first call
