@@ -22,8 +22,9 @@
 // merged in a fixed order by a finalize kernel (one workgroup per instance),
 // which also applies the solver's decision (stop test, CG scalars) to the
 // instance's state.  Calls
-// below a cutover level run in a persistent kernel, one workgroup per instance
-// with the levels in LDS.
+// below a cutover level run in a persistent kernel, one workgroup per instance:
+// k_subtree_regs with the levels in registers (damped Jacobi above a 1 x 1 or
+// 3 x 3 level), k_subtree with the levels in LDS (every other case).
 #include <math.h>
 
 #include <type_traits>
@@ -3042,8 +3043,8 @@ __global__ void __launch_bounds__(THREADS) k_subtree(SubArgs a)
 
 // ---------------------------------------------------------------------------
 // whole calls of damped-Jacobi cycles on a level of N x N points (N = 15, 31 or 63) of one instance,
-// coarsest level NC x NC (1 or 3), every level in registers.  k_subtree keeps the levels in LDS and
-// runs every other case (zebra, 7 x 7 coarsest levels, other sizes, lists of several sizes).
+// coarsest level NC x NC (1 or 3), every level in registers.  k_subtree keeps the levels in LDS and runs
+// every other case (zebra, 7 x 7 coarsest levels, other sizes, lists of several sizes, other options).
 //
 // What bounds a call is latency on one CU: a phase on 31 x 31 took 1900 cycles with the level in LDS
 // (23 LDS reads per thread of two points, 8 waves), a call on 15 x 15 9400 (3.9 us).  Here a level of

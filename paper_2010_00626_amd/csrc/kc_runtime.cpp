@@ -965,7 +965,8 @@ kc_status plan_exec(kc_hier* h)
         //   nu = 2, FP64, pre and post, 50 and 46 / 19 and 15.  The tiles' fused sibling calls still win
         //   below that (kappa = 3 cycles of 1023 x 1023 problems: 511 x 511 in tiles / strips with 2 problems
         //   269.5 / 270.2 us, 4 329 / 322; 255 x 255 with 4 322 / 327, 8 433 / 407; 127 x 127 with 8 407 / 437,
-        //   32 1036 / 975).
+        //   32 1036 / 975).  In FP32 the same lines hold (us of a cycle's launches on the level, kappa = 3, nu = 2,
+        //   tiles / strips: 511 x 511 with 4 problems 42 / 35, 255 x 255 with 8 92 / 60, 127 x 127 with 32 175 / 105).
         const int sn = h->ex.stream_n;
         if (f != strips && maxn > 0 && sn > 0) {
             const bool next = (f == 0 || f == 16) && 2 * maxn + 1 >= sn;
@@ -1144,8 +1145,8 @@ void iteration(kc_hier* h, int drv, const kc_cycle_params& c, std::vector<Launch
 {
     const bool f32 = h->prec == KC_F32_CYCLE;
     const int kappa = clamp_kappa(h, c.kappa);
-    // zebra relaxation always takes the one-kernel-per-operation schedule above the
-    // persistent kernel (the fused grid kernels are damped Jacobi)
+    // above the persistent kernel zebra relaxation takes gen_paper's schedule in either mode (a launch
+    // per colour; its transfers are fused outside the paper-structured mode)
     const bool paper = h->ex.mode == 1 || c.smoother == 1;
     switch (drv) {
     case DRV_CYCLE:
@@ -2173,7 +2174,7 @@ kc_status kc_time_stage(kc_hier* h, int32_t which, const kc_cycle_params* c, int
         L = sub(h, f32, d, clamp_kappa(h, c->kappa), true, c->nu1, c->nu2, false, FIN_NONE);
         for (int idx : h->lists[lt_sub(d)]) {
             const double n = h->hi[idx].il.n[d];
-            b += 2.0 * n * n * T;   // reads f, writes v of the top level; coarser levels stay in LDS
+            b += 2.0 * n * n * T;   // reads f, writes v of the top level; coarser levels stay on the CU
         }
     } else if (which == 3) {
         if (!f32) return fail(KC_ERR_STATE, "the refinement residual pass exists on FP32 hierarchies");
