@@ -1185,7 +1185,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_zebra(StageArgs a)
         // flags: bits 0-14 the line length from which an instance takes the registers mapping (0 never),
         // bits 15-29 that from which its y-lines take half as many lanes (0 never)
         const int from = a.flags & 0x7fff, quad_n = (a.flags >> 15) & 0x7fff;
-        if (from > 0 && nx >= from && nx + 1 >= P) {
+        if (from > 0 && nx >= from) {
             __shared__ T stage[GRID_THREADS * (P + 1) + 64];
             ZRegs<T, DIR, P> z;
             z.lgln = min(31 - __clz(nx + 1) - (P == 16 ? 4 : P == 8 ? 3 : 2), zebra_lg_most(DIR, quad_n > 0 && nx >= quad_n));

@@ -259,15 +259,18 @@ int lg_of(int n)
     return lg;
 }
 
-// zebra launches: an instance takes the registers mapping from this line length (0: never), if its line
-// fills a lane of the launch (the longest line gives the points per lane)
-int zebra_from(const kc_exec& e) { return e.zebra_wave_n > 0 ? std::max(e.zebra_wave_n, ZREG_N) : 0; }
+// zebra launches: an instance takes the registers mapping from this line length (0: never); its line has to
+// fill a lane of the launch (points per lane, from the longest line; 0 while that is not known)
+int zebra_from(const kc_exec& e, int points = 0)
+{
+    return e.zebra_wave_n > 0 ? std::max({e.zebra_wave_n, ZREG_N, points - 1}) : 0;
+}
 // blocks of one colour's lines of one instance: GRID_THREADS threads with (nx + 1) / points lanes per
 // line, 64 at most, in the registers mapping, else one thread per line (64 per block)
 int zebra_blocks(int lines, int nx, int from, int points)
 {
     const int per_colour = (lines + 1) / 2;
-    const int per_block = from > 0 && nx >= from && nx + 1 >= points ? GRID_THREADS / std::min((nx + 1) / points, 64) : 64;
+    const int per_block = from > 0 && nx >= from ? GRID_THREADS / std::min((nx + 1) / points, 64) : 64;
     return (per_colour + per_block - 1) / per_block;
 }
 int tiles_rect(int nx, int ny) { return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY); }
@@ -590,7 +593,7 @@ Launch sub(kc_hier* h, bool f32, int depth, int kappa, bool pair, int nu1, int n
 void zebra_args(kc_hier* h, int d, StageArgs& a)
 {
     a.zg = h->zpoints[d];
-    a.flags = zebra_from(h->ex) | (h->ex.zebra_quad_n << 15);
+    a.flags = zebra_from(h->ex, h->zpoints[d]) | (h->ex.zebra_quad_n << 15);
 }
 
 // fused schedule of one cycle: grid-wide PRE/POST above each instance's cut,
@@ -824,11 +827,11 @@ kc_status build_tables(kc_hier* h, const std::vector<char>* active)
             const bool lvl = d < L - 1 && hi.cut > d;
             if (h->semi) {   // rectangular levels; the coarsest line is solved by the zebra kernel
                 h->tiles[tt_lvl(d)][i + 1] = lvl ? tiles_rect(hi.il.nx[d], hi.il.n[d]) : 0;
-                h->tiles[tt_zeb(d)][i + 1] = d < L ? zebra_blocks(hi.il.n[d], hi.il.nx[d], zebra_from(h->ex), h->zpoints[d]) : 0;
+                h->tiles[tt_zeb(d)][i + 1] = d < L ? zebra_blocks(hi.il.n[d], hi.il.nx[d], zebra_from(h->ex, h->zpoints[d]), h->zpoints[d]) : 0;
                 continue;
             }
             h->tiles[tt_lvl(d)][i + 1] = lvl ? tiles_of(hi.il.n[d]) : 0;
-            h->tiles[tt_zeb(d)][i + 1] = lvl ? zebra_blocks(hi.il.n[d], hi.il.n[d], zebra_from(h->ex), h->zpoints[d]) : 0;
+            h->tiles[tt_zeb(d)][i + 1] = lvl ? zebra_blocks(hi.il.n[d], hi.il.n[d], zebra_from(h->ex, h->zpoints[d]), h->zpoints[d]) : 0;
             if (hi.cut == d && d < L) h->lists[lt_sub(d)].push_back(i);
             if (L - 1 == d) h->lists[lt_coarse(d)].push_back(i);
         }
