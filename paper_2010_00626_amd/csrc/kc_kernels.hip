@@ -1334,8 +1334,10 @@ __device__ __forceinline__ void band_sweeps(T (*sv)[RW * RH], const T* sf, const
 // three kernels of Algorithm 4 between the relaxation and the coarse call in
 // one; the post-smoothing kernel likewise adds the correction to A itself.
 // ---------------------------------------------------------------------------
-template <typename T, int NU, int TX, int TY>
-__global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
+// TO_A: the estimate goes to A, where a sibling junction reads it (a zero guess reads no estimate); a kernel of
+// its own, since choosing the buffer at run time costs 0.05 to 0.12 us of a small level's 2.7
+template <typename T, int NU, int TX, int TY, bool TO_A>
+__device__ __forceinline__ void pre_tile(const StageArgs& a)
 {
     constexpr int H = NU + 1;
     constexpr int RW = TX + 2 * H + 1, RH = TY + 2 * H + 1;
@@ -1350,9 +1352,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     const Tile t = tile_at<TX, TY>(blk, n);
     const int done = a.st[inst].done;
     const gp<const T> A = glob<T>((const void*)Lv.A);
-    const bool to_a = a.flags & FLAG_TO_A;   // on a zero guess, which reads no estimate
-    const gp<T> B = glob<T>(to_a ? Lv.A : Lv.B);
-    const int ldb = to_a ? Lv.lda : Lv.ldb;
+    const gp<T> B = glob<T>(TO_A ? Lv.A : Lv.B);
     const gp<const T> F = glob<T>((const void*)Lv.F);
     const T fs = (T)Lv.fscale;
     const int rx0 = t.x0 - H, ry0 = t.y0 - H;
@@ -1431,7 +1431,7 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
     for (int p = threadIdx.x; p < (in_place ? 0 : TX * TY); p += GRID_THREADS) {
         const int y = p / TX, x = p % TX;
         const int j = t.y0 + y, i = t.x0 + x;
-        if (j < n && i < n) B[(size_t)j * ldb + i] = vs[(H + y) * RW + (H + x)];
+        if (j < n && i < n) B[(size_t)j * (TO_A ? Lv.lda : Lv.ldb) + i] = vs[(H + y) * RW + (H + x)];
     }
     // residual on [x0, x0+TX] x [y0, y0+TY]
     if constexpr (TX == TY && TX <= 32) {
@@ -1457,6 +1457,18 @@ __global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
         }
     }
     if (a.fin == FIN_STOP) reduce_partial(a, nrm, Acc2());
+}
+
+template <typename T, int NU, int TX, int TY>
+__global__ void __launch_bounds__(GRID_THREADS) k_pre(StageArgs a)
+{
+    pre_tile<T, NU, TX, TY, false>(a);
+}
+
+template <typename T, int NU, int TX, int TY>
+__global__ void __launch_bounds__(GRID_THREADS) k_pre_a(StageArgs a)
+{
+    pre_tile<T, NU, TX, TY, true>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -3987,6 +3999,9 @@ static void pre_shape(const StageArgs& a, int nb, hipStream_t s)
         case 0: k_pre_s<T, NU, 16><<<nb, 256, 0, s>>>(a); break;
         default: k_pre_s<T, NU, 32><<<nb, 256, 0, s>>>(a); break;
         }
+    } else if (a.flags & FLAG_TO_A) {   // junctions run in 8 x 8 and 16 x 16 tiles
+        if (a.flags & 32) k_pre_a<T, NU, 8, 8><<<nb, GRID_THREADS, 0, s>>>(a);
+        else k_pre_a<T, NU, 16, 16><<<nb, GRID_THREADS, 0, s>>>(a);
     } else if (a.flags & 32) {
         k_pre<T, NU, 8, 8><<<nb, GRID_THREADS, 0, s>>>(a);
     } else if (a.flags & 1) {

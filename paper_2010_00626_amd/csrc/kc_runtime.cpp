@@ -1468,7 +1468,7 @@ std::string launch_name(const kc_hier* h, const Launch& L)
         return std::string("k_postpre<") + T + ", " + std::to_string(L.sa.src) + ", " + std::to_string(L.sa.nu) +
                (L.sa.flags == 32 ? ", 8, 8>" : ", 16, 16>");
     if (L.gk == GK_PRE || L.gk == GK_POST) {
-        const std::string k = L.gk == GK_PRE ? "k_pre" : "k_post";
+        const std::string k = L.gk == GK_POST ? "k_post" : L.sa.flags & FLAG_TO_A ? "k_pre_a" : "k_pre";
         const std::string nu = std::to_string(L.sa.nu);
         if (L.sa.flags & 2) return k + "_s<" + T + ", " + nu + ", " + std::to_string(16 << ((L.sa.flags >> 2) & 3)) + ">";
         if (L.sa.flags & 1) return k + "<" + T + ", " + nu + ", 16, 16>";
